@@ -415,14 +415,17 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
     } else {
         GSPM_HIP(launch_fill_u32(total, 0u, 3, hs));
     }
-    // 4. Emit (tile, record) pairs; the header gets the pair count and overflow flag.
+    // 4. Emit (tile, record) pairs; the header gets the pair count and overflow flag.  The
+    //    emitter also clears the per-tile work that the forward's waves raise.
+    GSPM_HIP(grow(ctx->twork, 4 * (P.n_tiles > 0 ? P.n_tiles : 1)));
+    uint32_t *twork = static_cast<uint32_t *>(ctx->twork.p);
     GSPM_HIP(launch_keygen(static_cast<uint32_t *>(ctx->dval_s.p), pack ? kPackMask : 0xffffffffu,
                            static_cast<uint32_t *>(ctx->dkey_s.p),
                            static_cast<uint32_t *>(ctx->offsets.p),
                            records, static_cast<const uint4 *>(ctx->spans.p), P.rs, R, g->n > 0 ? g->n : 1, P.vt,
                            static_cast<uint32_t *>(ctx->pkey.p),
                            static_cast<uint32_t *>(ctx->pval.p), hdr, (uint32_t)cap, total,
-                           static_cast<uint32_t *>(ctx->big.p), total + 1, n_live, ranges, P.n_tiles, hs));
+                           static_cast<uint32_t *>(ctx->big.p), total + 1, n_live, ranges, twork, P.n_tiles, hs));
     t_bin.stop();
     // 5. Stable sort by tile id; its final pass writes the per-tile ranges (6).
     if (cap > 0) {
@@ -436,8 +439,6 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
     // Heaviest tiles first: by list length for the forward; the forward measures each
     // tile's contributing depth, which orders the backward.
     uint32_t *order = at<uint32_t>(frame_state, L0.order);
-    GSPM_HIP(grow(ctx->twork, 4 * (P.n_tiles > 0 ? P.n_tiles : 1)));
-    uint32_t *twork = static_cast<uint32_t *>(ctx->twork.p);
     GSPM_HIP(launch_order_tiles(ranges, nullptr, P.n_tiles, order, hs));
     // 7. Composite (optionally marking the records that contribute to a pixel).
     uint8_t *visible = nullptr;

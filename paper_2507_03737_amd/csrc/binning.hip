@@ -597,7 +597,8 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
          RasterSettings rs, int64_t n_records, int64_t n_per_view, ViewTable vt, uint32_t *__restrict__ pkey,
          uint32_t *__restrict__ pval, FrameHeader *__restrict__ hdr, uint32_t cap,
          const uint32_t *__restrict__ total, uint32_t *__restrict__ big_list, uint32_t *__restrict__ big_count,
-         const uint32_t *__restrict__ n_dev, uint2 *__restrict__ ranges, int64_t n_tiles) {
+         const uint32_t *__restrict__ n_dev, uint2 *__restrict__ ranges, uint32_t *__restrict__ twork,
+         int64_t n_tiles) {
     __shared__ uint32_t row_pos[kKeygenWaves][kKeygenRows];   // first output position
     __shared__ uint32_t row_tile[kKeygenWaves][kKeygenRows];  // global tile id of the first tile
     __shared__ uint32_t row_rec[kKeygenWaves][kKeygenRows];   // record index
@@ -606,7 +607,11 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
     const int wid = threadIdx.x / kWave, lane = lane_id();
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     // Empty tile ranges, for the tile sort's last pass to narrow (here to save a launch).
-    for (int64_t t = p; t < n_tiles; t += (int64_t)gridDim.x * blockDim.x) ranges[t] = make_uint2(0xffffffffu, 0u);
+    // The per-tile work that the forward's waves raise starts at 0.
+    for (int64_t t = p; t < n_tiles; t += (int64_t)gridDim.x * blockDim.x) {
+        ranges[t] = make_uint2(0xffffffffu, 0u);
+        twork[t] = 0u;
+    }
     if (p == 0) {
         // Everything a backward checks before it reads the frame state.
         const uint32_t t = *total;
@@ -886,12 +891,12 @@ hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const ui
                          int64_t n_records, int64_t n_per_view,
                          const ViewTable &vt, uint32_t *pkey, uint32_t *pval, FrameHeader *hdr, uint32_t capacity,
                          const uint32_t *total, uint32_t *big_list, uint32_t *big_count, const uint32_t *n_dev,
-                         uint2 *ranges, int64_t n_tiles, hipStream_t s) {
+                         uint2 *ranges, uint32_t *twork, int64_t n_tiles, hipStream_t s) {
     const float4 *rec = reinterpret_cast<const float4 *>(records);
     const int64_t nb = n_records > 0 ? (n_records + 255) / 256 : 1;
     hipLaunchKernelGGL(k_keygen, dim3((unsigned)nb), dim3(256), 0, s, sorted_rec, rec_mask, sorted_counts, offsets, rec,
                        spans, rs, n_records, n_per_view, vt, pkey, pval, hdr, capacity, total, big_list, big_count,
-                       n_dev, ranges, n_tiles);
+                       n_dev, ranges, twork, n_tiles);
     if (n_records > 0)
         hipLaunchKernelGGL(k_keygen_big, dim3(1024), dim3(256), 0, s, sorted_rec, rec_mask, offsets, rec, rs,
                            n_per_view, vt, pkey, pval, capacity, big_list, big_count);

@@ -41,13 +41,17 @@ struct RasterSettings {
 //   r1 = (a, b, c, opacity)           factored conic, base 2:
 //                                     alpha = opacity * 2^-((a dx + b dy)^2 + (c dy)^2)
 //   r2 = (c_r, c_g, c_b, z)           colour and camera depth
-//   r3 = (p_x, p_y, p_z, 0)           composited point (world centre or camera centre)
+//   r3 = (p_x, p_y, p_z, t)           composited point (world centre or camera centre) and
+//                                     the acceptance threshold t = -log2(alpha_min / opacity)
 // With k = log2(e) / 2, k Q = L^T L for L = [[a, b], [0, c]] (the Cholesky factor of the
 // scaled conic Q).  The exponent is a sum of two squares: an elongated footprint (a near
 // Gaussian seen at a grazing angle) would lose ~1e-4 of alpha to cancellation between the
 // terms of the expanded form A dx^2 + B dx dy + C dy^2 in float32, the factored form
 // keeps it near float32 rounding.
 constexpr int kRecFloats = 16;
+
+// alpha = opacity 2^-s reaches alpha_min exactly when s <= this threshold.
+__device__ inline float accept_threshold(float alpha_min, float opacity) { return -__log2f(alpha_min / opacity); }
 
 // Per-record image-plane gradient accumulator (16 floats, 13 used).  With
 // g = alpha dL/dalpha per composited fragment (0 where alpha is clamped) and (dx, dy) the
@@ -451,14 +455,14 @@ hipError_t radix_sort(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t
 // more than kBigRecord pairs are queued in big_list (big_count must be zero on entry: the
 // pair-offset scan clears it) and emitted by whole waves.  records: the projected records (for the support footprint of records
 // whose spans are not cached in spans).  It also fills ranges [n_tiles] with the empty
-// range (0xffffffff, 0) that the tile sort's last pass narrows.
+// range (0xffffffff, 0) that the tile sort's last pass narrows, and twork [n_tiles] with 0.
 // rec_mask: kPackMask if sorted_rec carries packed counts, else all ones.
 hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const uint32_t *sorted_counts,
                          const uint32_t *offsets, const float *records, const uint4 *spans, const RasterSettings &rs,
                          int64_t n_records, int64_t n_per_view,
                          const ViewTable &vt, uint32_t *pkey, uint32_t *pval, FrameHeader *hdr,
                          uint32_t capacity, const uint32_t *total, uint32_t *big_list, uint32_t *big_count,
-                         const uint32_t *n_dev, uint2 *ranges, int64_t n_tiles, hipStream_t s);
+                         const uint32_t *n_dev, uint2 *ranges, uint32_t *twork, int64_t n_tiles, hipStream_t s);
 
 hipError_t launch_sum_u64(const uint32_t *x, int64_t n, unsigned long long *out, hipStream_t s);
 
@@ -500,8 +504,8 @@ hipError_t launch_order_tiles(uint2 *ranges, const uint32_t *work, int64_t n_til
 
 bool raster_config_supported(int tile, int ppt);
 
-// order: workgroup -> tile (NULL: identity).  tile_work (optional) receives each tile's
-// largest per-pixel list count up to the last contributing fragment.
+// order: launch slot -> tile (NULL: identity).  tile_work (zero on entry) receives each tile's
+// largest per-pixel bound on the contributing list entries (`last`).
 hipError_t launch_raster_forward(const ViewTable &vt, const RasterSettings &rs, const uint2 *ranges,
                                  const uint32_t *pair_vals, const float *records, float *rgb,
                                  float *depth, float *alpha, float *pointmap, float *t_final,

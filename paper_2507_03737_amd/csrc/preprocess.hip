@@ -156,10 +156,11 @@ k_preprocess(gspm_gaussians G, ViewTable vt, const float *__restrict__ T_cw, Ras
                 o[0] = r0;
                 o[1] = r1;
                 o[2] = make_float4(G.rgb[g], G.rgb[n + g], G.rgb[2 * n + g], zf);
+                const float thr = accept_threshold(rs.alpha_min, r1.w);
                 if (rs.frame == 0)
-                    o[3] = make_float4(G.means[g], G.means[n + g], G.means[2 * n + g], 0.0f);
+                    o[3] = make_float4(G.means[g], G.means[n + g], G.means[2 * n + g], thr);
                 else
-                    o[3] = make_float4((float)P.m[0], (float)P.m[1], (float)P.m[2], 0.0f);
+                    o[3] = make_float4((float)P.m[0], (float)P.m[1], (float)P.m[2], thr);
                 // Number of tiles the support meets, row by row (the pair emission repeats this).
                 // Records whose support box covers many tiles are counted by whole waves instead.
                 Footprint f;

@@ -15,6 +15,9 @@
 // threshold, so the exponential is only evaluated for pixels that composite it; the
 // workgroup stops as soon as every pixel has reached the transmittance floor.
 //
+// Windows with few waves are composited by independent waves instead (k_raster_fwd_waves): the
+// same expressions per pixel in the same order, so the same images.
+//
 // The forward also records, per wave, which list entries one of its live pixels accepted
 // (one bit per entry and wave, kept in the frame state).  The backward walks only those
 // entries, front to back: in the matrix-core form each wave stages its own entries through
@@ -39,6 +42,7 @@ namespace gspm {
 
 namespace {
 
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 struct TilePos {
     int gt;  // global tile index
@@ -52,9 +56,9 @@ struct TilePos {
 // Workgroups run the tiles in the given order (heaviest first, so that the long lists do
 // not start last and leave the chip idle behind them).
 template <int TILE>
-__device__ inline TilePos tile_pos(const ViewTable &vt, const uint32_t *order) {
+__device__ inline TilePos tile_pos(const ViewTable &vt, const uint32_t *order, uint32_t slot) {
     TilePos p;
-    const int gt = order ? (int)order[blockIdx.x] : (int)blockIdx.x;
+    const int gt = order ? (int)order[slot] : (int)slot;
     p.gt = gt;
     p.v = find_view(vt, gt);
     const int lt = gt - vt.tile_off[p.v];
@@ -69,8 +73,8 @@ __device__ inline TilePos tile_pos(const ViewTable &vt, const uint32_t *order) {
     return p;
 }
 
-// Stage record r into LDS slot q, in tile-local pixel coordinates, with the threshold
-// -e_min, e_min = log2(alpha_min / opacity): alpha >= alpha_min exactly when the base-2
+// Stage record r into LDS slot q, in tile-local pixel coordinates, with the record's
+// threshold -e_min (see accept_threshold): alpha >= alpha_min exactly when the base-2
 // exponent e = -s >= e_min, i.e. s <= -e_min, so rejected pixels never evaluate the
 // exponential.
 //   s0 = (u, v, a, b), s1 = (c, -e_min, opacity, record index), s2 = (colour, z), s3 = point
@@ -78,14 +82,14 @@ __device__ inline TilePos tile_pos(const ViewTable &vt, const uint32_t *order) {
 // The acceptance test reads s0 and s1 only.
 // With a list position pos, it replaces the point's unused fourth component (one 16-byte
 // write instead of that write and a 4-byte one at a 16-byte stride, a 4-way conflict).
-__device__ inline void stage(const float4 *__restrict__ rec, uint32_t r, float x0, float y0, float alpha_min,
-                             float4 *s0, float4 *s1, float4 *s2, float4 *s3, int q, const uint32_t *pos = nullptr) {
+__device__ inline void stage(const float4 *__restrict__ rec, uint32_t r, float x0, float y0, float4 *s0, float4 *s1,
+                             float4 *s2, float4 *s3, int q, const uint32_t *pos = nullptr) {
     const float4 *src = rec + 4 * (int64_t)r;
     const float4 a = src[0], b = src[1], c = src[2], d = src[3];
     const float ul = (a.x - x0) + a.z;
     const float vl = (a.y - y0) + a.w;
     s0[q] = make_float4(ul, vl, b.x, b.y);
-    s1[q] = make_float4(b.z, -__log2f(alpha_min / b.w), b.w, __uint_as_float(r));
+    s1[q] = make_float4(b.z, d.w, b.w, __uint_as_float(r));
     s2[q] = c;
     s3[q] = pos ? make_float4(d.x, d.y, d.z, __uint_as_float(*pos)) : d;
 }
@@ -111,12 +115,13 @@ struct Layout {
     static constexpr int WW = kWave * PPT / WH;
     static constexpr bool CULL = NW > 1;  // a single wave owns the whole tile: binning culled already
     static_assert(WW * WH == kWave * PPT && TILE % WW == 0 && TILE % WH == 0, "unsupported raster shape");
+    int w;                       // wave index within the tile
     int lx, ly;                  // tile-local column and first row of this lane
     float rx0, rx1, ry0, ry1;    // this wave's rectangle of pixel centres, tile-local
-    int w;                       // wave index within the workgroup
-    __device__ Layout() {
-        // The wave index is uniform: keep it (and the rectangle) in scalar registers.
-        w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    // Of a workgroup of all the tile's waves, this thread's.  The wave index is uniform: keep
+    // it (and the rectangle) in scalar registers.
+    __device__ Layout() : Layout(__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave))) {}
+    __device__ explicit Layout(int wave) : w(wave) {
         const int lane = lane_id();
         const int wx = (w % (TILE / WW)) * WW, wy = (w / (TILE / WW)) * WH;
         lx = wx + lane % WW;
@@ -174,6 +179,15 @@ __device__ inline uint64_t batch_mask(const float4 *s0, const float4 *s1, int c,
     return ballot(q < cnt && meets_rect(a, b, x0, x1, y0, y1));
 }
 
+// This lane's bit of a lane mask, as the predicate of a select (the mask itself serves as it).
+__device__ inline bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
+// Orders a wave's LDS accesses across lanes (a wave's LDS instructions complete in order).
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // FRAME is the pointmap frame (0 world, 1 camera, 2 from the depth, Eq. 5).  In the
 // camera frame the depth is the composited point's z and is not accumulated twice; in
 // frame 2 the point is not accumulated at all.  COUNT: also write each pixel's number of
@@ -191,12 +205,12 @@ k_raster_fwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
     __shared__ float4 s0[NT], s1[NT], s2[NT], s3[NT];
     __shared__ uint32_t block_work;
     __shared__ uint32_t block_walk[2];  // COUNT: list entries walked and accepted by the waves
-    const TilePos tp = tile_pos<TILE>(vt, order);
+    const TilePos tp = tile_pos<TILE>(vt, order, blockIdx.x);
     const uint2 rg = ranges[tp.gt];
     const L lay;
     const int lx = lay.lx, ly = lay.ly;
     const float px = (float)lx;
-    const float amin = rs.alpha_min, amax = rs.alpha_max, tmin = rs.t_min;
+    const float amax = rs.alpha_max, tmin = rs.t_min;
     const int i = tp.tx * TILE + lx;
 
     float T[PPT], C0[PPT], C1[PPT], C2[PPT], D[PPT], X0[PPT], X1[PPT], X2[PPT];
@@ -248,7 +262,7 @@ k_raster_fwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
         const uint32_t kk = base + threadIdx.x;
         const uint32_t vcur = vnext;
         if (kk + NT < rg.y) vnext = vals[kk + NT];
-        if (kk < rg.y) stage(rec, vcur, tp.x0, tp.y0, amin, s0, s1, s2, s3, threadIdx.x);
+        if (kk < rg.y) stage(rec, vcur, tp.x0, tp.y0, s0, s1, s2, s3, threadIdx.x);
         __syncthreads();
         const int cnt = (int)min((uint32_t)NT, rg.y - base);
         for (int c = 0; c < cnt && wave_live; c += kWave) {
@@ -373,7 +387,7 @@ k_raster_fwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
             atomicAdd(reinterpret_cast<unsigned long long *>(&hdr->accepted), (unsigned long long)block_walk[1]);
         }
     }
-    if (tile_work) {  // uniform
+    {
         if (threadIdx.x == 0) block_work = 0u;
         __syncthreads();
         uint32_t m = 0u;
@@ -384,6 +398,254 @@ k_raster_fwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
         __syncthreads();
         if (threadIdx.x == 0) tile_work[tp.gt] = block_work;
     }
+}
+
+// Launch of independent waves, one to a workgroup: workgroup b -> (slot of the tile order,
+// wave of the tile).  Workgroups go to the 8 XCDs in turn: the waves of a tile are 8 apart, so
+// that they run on one XCD and share its L2.
+template <int NW>
+inline uint32_t wave_grid(int n_tiles) {
+    return (uint32_t)((n_tiles + 7) / 8 * 8 * NW);
+}
+template <int NW>
+__device__ inline void wave_place(uint32_t b, uint32_t &slot, int &w) {
+    slot = b / (8 * NW) * 8 + (b & 7u);
+    w = (int)(b / 8 % NW);
+}
+
+constexpr int kChunk = kWave;       // list entries staged at a time
+constexpr int kPlane = kChunk + 2;  // words of a staging plane: quad-lane writes without bank conflicts
+// A stopped pixel's row: a quiet NaN carrying the chunk slot of the entry that stopped it.
+constexpr uint32_t kNan = 0x7fc00000u, kNanStop = 0x7fc00040u;
+
+// Forward compositing by independent waves (one pixel per lane): a wave owns its rectangle of a
+// tile and walks the tile's list on its own, with no barrier.  It is bound by the latency of
+// the longest waves where the launch holds only a few rounds of them: the workgroup form above
+// meets at two barriers per 256 entries, where the busiest wave walks 1.34-1.41 times the mean,
+// and walks one entry at a time, waiting for its LDS reads and its exponent each.
+//
+// Per 64 entries: the records arrive four lanes per record (one 16-byte word each, loaded one
+// chunk ahead: 16 lines per load instead of 64), go to four LDS planes, and lane q converts
+// record q to tile-local coordinates and tests it against the rectangle of the wave's live
+// pixels.  The survivors are walked in pairs, so that the LDS latency, the tests and the
+// exponents of two entries overlap.
+template <int TILE, int FRAME, bool MARK>
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5)))
+k_raster_fwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges,
+                   const uint32_t *__restrict__ vals, const float4 *__restrict__ rec, float *__restrict__ out_rgb,
+                   float *__restrict__ out_depth, float *__restrict__ out_alpha, float *__restrict__ out_pm,
+                   float *__restrict__ t_final, uint32_t *__restrict__ last, uint8_t *__restrict__ visible,
+                   const uint32_t *__restrict__ order, uint32_t *__restrict__ tile_work,
+                   uint64_t *__restrict__ wmask, int64_t wstride) {
+    using L = Layout<TILE, 1>;
+    __shared__ float4 st[4 * kPlane];
+    uint32_t tslot;
+    int wv;
+    wave_place<L::NW>(blockIdx.x, tslot, wv);
+    if (tslot >= (uint32_t)vt.tile_off[vt.n_views]) return;
+    const TilePos tp = tile_pos<TILE>(vt, order, tslot);
+    const uint2 rg = ranges[tp.gt];
+    const L lay(wv);
+    const int lane = lane_id();
+    const float px = (float)lay.lx;
+    const float amax = rs.alpha_max, tmin = rs.t_min;
+    const int i = tp.tx * TILE + lay.lx, j = tp.ty * TILE + lay.ly;
+    const bool inside = i < tp.W && j < tp.H;
+
+    float T = 1.0f, C0 = 0.f, C1 = 0.f, C2 = 0.f, D = 0.f, X0 = 0.f, X1 = 0.f, X2 = 0.f;
+    // The pixel's tile-local row while it composites; NaN once it has stopped (or if it
+    // lies outside the view), which makes the exponent NaN, so that the acceptance test
+    // stays one comparison whose lane mask is the wave's ballot as it stands.
+    float py = inside ? (float)lay.ly : __uint_as_float(kNan);
+    // A bound on the list entries that the backward considers: an entry before it contributes
+    // to the pixel exactly when its alpha reaches alpha_min.  A stopped pixel's is the entry
+    // that stopped it; otherwise the end of the last chunk in which it composited.
+    uint32_t n_last = 0u;
+    uint64_t live = ballot(py == py);  // lanes that still composite, re-evaluated once per chunk
+    // The rectangle of the wave's live pixels, which the chunks are culled against: once
+    // pixels stop, the entries that only they would take are not walked.  Scalar bit work on
+    // the live-lane mask (lane = column + WW x row).
+    float lrx0 = lay.rx0, lrx1 = lay.rx1, lry0 = lay.ry0, lry1 = lay.ry1;
+    auto live_rect = [&]() {
+        uint64_t cols = live;
+#pragma unroll
+        for (int sh = 32; sh >= L::WW; sh >>= 1) cols |= cols >> sh;
+        cols &= (1ull << L::WW) - 1ull;
+        const int c0 = (int)__builtin_ctzll(cols), c1 = 63 - (int)__builtin_clzll(cols);
+        lrx0 = lay.rx0 + (float)c0;
+        lrx1 = lay.rx0 + (float)c1;
+        lry0 = lay.ry0 + (float)((int)__builtin_ctzll(live) / L::WW);
+        lry1 = lay.ry0 + (float)((63 - (int)__builtin_clzll(live)) / L::WW);
+    };
+    if (live != 0ull) live_rect();
+
+    // Lane 4 i + w holds word w of records 16 r + i (r = 0..3) of a chunk.  The records are
+    // loaded one chunk ahead and their indices two, so that a step waits on no load it has
+    // just issued.  Entries past the list's end stage its last one, which no mask holds.
+    const uint32_t n = rg.y - rg.x;
+    const uint32_t *list = vals + rg.x;
+    uint32_t nidx[4];
+    v4f raw[4];  // a plain vector: as an array of float4 it would live in scratch memory
+    auto load_idx = [&](uint32_t c0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) nidx[r] = list[min(c0 + 16u * r + ((uint32_t)lane >> 2), n - 1u)];
+    };
+    auto load_raw = [&]() {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) raw[r] = reinterpret_cast<const v4f *>(rec)[4 * (int64_t)nidx[r] + (lane & 3)];
+    };
+    if (live != 0ull && n != 0u) {
+        load_idx(0u);
+        load_raw();
+        if (n > (uint32_t)kChunk) load_idx(kChunk);
+    }
+    for (uint32_t c0 = 0u; c0 < n && live != 0ull; c0 += kChunk) {
+        wave_sync();  // the previous chunk has been read
+        v4f *dst = reinterpret_cast<v4f *>(st) + (lane & 3) * kPlane + (lane >> 2);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dst[16 * r] = raw[r];
+        wave_sync();
+        if (c0 + kChunk < n) {
+            load_raw();
+            if (c0 + 2 * kChunk < n) load_idx(c0 + 2 * kChunk);
+        }
+        // (u, v, a, b), (c, threshold, opacity, NaN | q) of record q = this lane.
+        const float4 r0 = st[lane], r1 = st[kPlane + lane], r3 = st[3 * kPlane + lane];
+        asm volatile("" ::"v"(r3.x), "v"(r3.y), "v"(r3.z), "v"(r3.w));  // 16 bytes: no bank conflicts
+        const float4 sa = make_float4((r0.x - tp.x0) + r0.z, (r0.y - tp.y0) + r0.w, r1.x, r1.y);
+        const float4 sb = make_float4(r1.z, r3.w, r1.w, __uint_as_float(kNanStop | (uint32_t)lane));
+        uint64_t m = ballot((!L::CULL || meets_rect(sa, sb, lrx0, lrx1, lry0, lry1)) && c0 + (uint32_t)lane < n);
+        st[lane] = sa;
+        st[kPlane + lane] = sb;
+        wave_sync();
+        const float T0 = T;
+        uint64_t composited = 0ull;  // entries of this chunk accepted by one of the wave's live pixels
+        uint64_t marked = 0ull;      // MARK: entries that contribute to a pixel
+        // Reads entry q (its words at one address for the whole wave: 16-byte reads; a
+        // 12-byte one keeps the LDS busy twice as long as a 16-byte one, an 8-byte one half
+        // as long).  In the camera frame the point's z is the depth, the colour's fourth word.
+        auto fetch = [&](int q, float4 &a, float4 &b, float4 &cc, float4 &d) {
+            a = st[q];
+            b = st[kPlane + q];
+            cc = st[2 * kPlane + q];
+            if (FRAME == 0) d = st[3 * kPlane + q];
+            if (FRAME == 1) {
+                const float2 xy = *reinterpret_cast<const float2 *>(&st[3 * kPlane + q]);
+                d = make_float4(xy.x, xy.y, cc.w, 0.f);
+            }
+            if (FRAME == 2) d = make_float4(0.f, 0.f, 0.f, 0.f);
+            asm volatile("" ::"v"(cc.w));  // whole 16-byte reads where three words are used
+            if (FRAME == 0) asm volatile("" ::"v"(d.w));
+        };
+        auto exponent = [&](const float4 &a, const float4 &b) {
+            const float dx = px - a.x;
+            return quad_s(a.z * dx, a.w, b.x, py - a.y);
+        };
+        // One entry's share of the wave's pixels, which may stop some of them (ok: the lanes
+        // that accept it; stopped lanes leave ok_next, the next entry's).  may_clamp: some
+        // opacity of the chunk reaches alpha_max (otherwise o exp2(-s) <= o < alpha_max and the
+        // clamp is the identity).
+        auto composite = [&](auto may_clamp, int q, const float4 &b, const float4 &cc, const float4 &d, float sq,
+                             uint64_t ok, uint64_t &ok_next) {
+            // Some live pixel accepts the entry: it is composited there or stops that pixel.
+            // The backward walks these entries (a superset of those it finds a valid pixel for;
+            // it skips the rest), scalar work only.
+            composited |= ok != 0ull ? 1ull << q : 0ull;
+            float al = b.z * __builtin_amdgcn_exp2f(-sq);
+            if (decltype(may_clamp)::value) al = clamp_alpha(al, amax);
+            const float Tn = fmaf(-al, T, T);  // T (1 - alpha), rounded once
+            // One comparison; the lane masks combine in scalar code.
+            const uint64_t over = ballot(!(Tn < tmin));
+            const uint64_t add = ok & over, stop = ok & ~over;
+            ok_next &= ~stop;
+            if (MARK) marked |= add != 0ull ? 1ull << q : 0ull;
+            const float w = in_mask(add) ? __fmul_rn(al, T) : 0.0f;
+            C0 = fmaf(w, cc.x, C0);
+            C1 = fmaf(w, cc.y, C1);
+            C2 = fmaf(w, cc.z, C2);
+            if (FRAME != 1) D = fmaf(w, cc.w, D);
+            if (FRAME != 2) {
+                X0 = fmaf(w, d.x, X0);
+                X1 = fmaf(w, d.y, X1);
+                X2 = fmaf(w, d.z, X2);
+            }
+            T = in_mask(add) ? Tn : T;
+            py = in_mask(stop) ? b.w : py;  // NaN with the entry's slot
+        };
+        auto walk_pairs = [&](auto may_clamp) {
+            for (int p = (int)__popcll(m) >> 1; p > 0; --p) {
+                const int q0 = (int)__builtin_ctzll(m);
+                m ^= 1ull << q0;
+                const int q1 = (int)__builtin_ctzll(m);
+                m ^= 1ull << q1;
+                float4 a0, b0, e0, d0, a1, b1, e1, d1;
+                fetch(q0, a0, b0, e0, d0);
+                fetch(q1, a1, b1, e1, d1);
+                asm volatile("" ::"v"(b0.w), "v"(b1.w));
+                const float s0 = exponent(a0, b0), s1 = exponent(a1, b1);
+                uint64_t ok0 = ballot(s0 <= b0.y), ok1 = ballot(s1 <= b1.y), none = 0ull;
+                composite(may_clamp, q0, b0, e0, d0, s0, ok0, ok1);
+                composite(may_clamp, q1, b1, e1, d1, s1, ok1, none);
+            }
+        };
+        if ((ballot(sb.z >= amax) & m) != 0ull) walk_pairs(std::true_type{});
+        else walk_pairs(std::false_type{});
+        if (m != 0ull) {  // the last of an odd number
+            const int q = (int)__builtin_ctzll(m);
+            float4 a, b, cc, d;
+            fetch(q, a, b, cc, d);
+            asm volatile("" ::"v"(b.w));
+            const float sq = exponent(a, b);
+            uint64_t none = 0ull;
+            composite(std::true_type{}, q, b, cc, d, sq, ballot(sq <= b.y), none);
+        }
+        if (MARK) {
+            if ((marked >> lane) & 1ull) visible[list[c0 + (uint32_t)lane]] = 1;
+        }
+        if (composited != 0ull && lane == 0) {
+            // Entry q sits at list position rg.x + c0 + q; the chunk's bits straddle at most
+            // two words of this wave's plane.
+            const uint64_t pos = (uint64_t)rg.x + c0;
+            uint64_t *w = wmask + (int64_t)wv * wstride + (int64_t)(pos >> 6);
+            const int sh = (int)(pos & 63u);
+            atomicOr((unsigned long long *)w, (unsigned long long)(composited << sh));
+            if (sh != 0) atomicOr((unsigned long long *)(w + 1), (unsigned long long)(composited >> (64 - sh)));
+        }
+        n_last = T != T0 ? min(c0 + (uint32_t)kChunk, n) : n_last;
+        const uint64_t now = ballot(py == py);
+        if (now != live) {  // wave-uniform: some pixels stopped in this chunk
+            const uint32_t pb = __float_as_uint(py);
+            if ((pb & ~63u) == kNanStop) {
+                n_last = c0 + (pb & 63u);
+                py = __uint_as_float(kNan);
+            }
+            live = now;
+            if (live != 0ull) live_rect();
+        }
+    }
+    if (inside) {
+        const int64_t e = (int64_t)j * tp.W + i;
+        const int64_t pix = tp.pix_off + e, o3 = 3 * tp.pix_off + e, plane = tp.plane;
+        out_rgb[o3] = fmaf(T, rs.bg[0], C0);
+        out_rgb[o3 + plane] = fmaf(T, rs.bg[1], C1);
+        out_rgb[o3 + 2 * plane] = fmaf(T, rs.bg[2], C2);
+        const float depth = FRAME == 1 ? X2 : D;
+        out_depth[pix] = depth;
+        out_alpha[pix] = 1.0f - T;
+        if (FRAME == 2) {
+            X0 = depth * (((float)i - vt.cx[tp.v]) / vt.fx[tp.v]);
+            X1 = depth * (((float)j - vt.cy[tp.v]) / vt.fy[tp.v]);
+            X2 = depth;
+        }
+        out_pm[o3] = X0;
+        out_pm[o3 + plane] = X1;
+        out_pm[o3 + 2 * plane] = X2;
+        t_final[pix] = T;
+        last[pix] = n_last;
+    }
+    uint32_t work = n_last;  // the tile's deepest entry: the largest over its waves (cleared before the launch)
+    for (int off = 32; off > 0; off >>= 1) work = max(work, (uint32_t)__shfl_xor((int)work, off, 64));
+    if (lane == 0 && work != 0u) atomicMax(tile_work + tp.gt, work);
 }
 
 __device__ inline float load_or0(const float *p, int64_t i) { return p ? p[i] : 0.0f; }
@@ -462,12 +724,12 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
     // Slot s's record (mean, index) follows at kMeta + 4 s: (u, v, -, index).
     constexpr int kBq = 256, kBc = 64, kMeta = 4 * kBq;
     __shared__ __align__(16) float mf_b[kMfma ? L::NW : 1][kMfma ? kMeta + 4 * kSlots : 4];
-    const TilePos tp = tile_pos<TILE>(vt, order);
+    const TilePos tp = tile_pos<TILE>(vt, order, blockIdx.x);
     const uint2 rg = ranges[tp.gt];
     const L lay;
     const int lx = lay.lx, ly = lay.ly;
     const float px = (float)lx;
-    const float amin = rs.alpha_min, amax = rs.alpha_max;
+    const float amax = rs.alpha_max;
     const int i = tp.tx * TILE + lx;
     // Per-pixel upstream gradient and, to start the walk's remainder Rem, the total
     // G = sum_k w_k (g . e_k) + T_final (g_C . bg) that the forward's outputs give.
@@ -539,7 +801,6 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
     // (F, 16 values per lane) is constant for the wave; the B operand (g and w of each
     // slot) is written by the walk.  Lane L supplies A[L % 16][4 kb + L / 16] and
     // B[4 kb + L / 16][L % 16] for step kb and receives D[4 (L / 16) + r][L % 16].
-    typedef float v4f __attribute__((ext_vector_type(4)));
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
     float Aop[kMfma ? 16 : 1];
     // Byte offset of this lane's pixel in column 0 (bits 4-6 clear), with its word's XOR
@@ -797,7 +1058,7 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
                     const uint32_t si = (uint32_t)__popc(mh & ((1u << sub) - 1u));
                     const uint32_t p = pos + (uint32_t)lane;
                     const uint32_t rel = p - rg.x;
-                    stage(rec, my_rec, tp.x0, tp.y0, amin, w0, w1, w2, w3, (int)si, &rel);
+                    stage(rec, my_rec, tp.x0, tp.y0, w0, w1, w2, w3, (int)si, &rel);
                 }
                 __builtin_amdgcn_wave_barrier();  // staged (a wave's LDS accesses stay in order)
                 const int n_st = __popc(mh);
@@ -822,7 +1083,7 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
             const uint32_t vcur = vnext;
             if (threadIdx.x < NS && kk + NS < end) vnext = vals[kk + NS];
             const uint64_t bits0 = use_bits ? wave_bits(base) : 0ull;  // read while the batch is staged
-            if (threadIdx.x < NS && kk < end) stage(rec, vcur, tp.x0, tp.y0, amin, s0, s1, s2, s3, threadIdx.x);
+            if (threadIdx.x < NS && kk < end) stage(rec, vcur, tp.x0, tp.y0, s0, s1, s2, s3, threadIdx.x);
             __syncthreads();
             const int cnt = (int)min((uint32_t)NS, end - base);
             const uint32_t rel0 = base - rg.x;
@@ -871,6 +1132,15 @@ bool raster_config_supported(int tile, int ppt) {
     return false;
 }
 
+// Windows of at most this many waves (at one pixel per lane) are composited by independent
+// waves, larger ones by workgroups that share their staging.  The chip holds 5120 of these
+// waves at once; up to about ten rounds of them the longest waves' latency decides (960x640
+// with 500k Gaussians, 9.6k waves: 135 against 191 us; 1216x352 with 300k, 6.7k waves: 68
+// against 103 us), at 58k waves (8 keyframes, 1M Gaussians) the two take the same time (656 and
+// 667 us: vector issue binds both), and at 522k (16 x 1920x1080, 3M Gaussians) the second
+// reading of each record by every wave costs 6% (4.47 against 4.21 ms).
+constexpr int64_t kIndependentWaves = 65536;
+
 hipError_t launch_raster_forward(const ViewTable &vt, const RasterSettings &rs, const uint2 *ranges,
                                  const uint32_t *pair_vals, const float *records, float *rgb, float *depth,
                                  float *alpha, float *pointmap, float *t_final, uint32_t *last, uint32_t *contrib,
@@ -879,13 +1149,26 @@ hipError_t launch_raster_forward(const ViewTable &vt, const RasterSettings &rs, 
     const int n_tiles = vt.tile_off[vt.n_views];
     const float4 *rec = reinterpret_cast<const float4 *>(records);
     if (rs.frame < 0 || rs.frame > 2) return hipErrorInvalidValue;
+    // The work counts come from the workgroup form only.
+    const bool waves = vt.ppt == 1 && !rs.count_work &&
+                       (int64_t)n_tiles * (vt.tile * vt.tile / kWave) <= kIndependentWaves;
+#define GSPM_FWDW(T_, F_, M_)                                                                                  \
+    hipLaunchKernelGGL((k_raster_fwd_waves<T_, F_, M_>), dim3(wave_grid<Layout<T_, 1>::NW>(n_tiles)), dim3(kWave), \
+                       0, s, vt, rs, ranges, pair_vals, rec, rgb, depth, alpha, pointmap, t_final, last, visible,    \
+                       order, tile_work, wmask, wstride)
+#define GSPM_FWDW1(T_, F_)                        \
+    do {                                          \
+        if (visible) GSPM_FWDW(T_, F_, true);     \
+        else GSPM_FWDW(T_, F_, false);            \
+    } while (0)
 #define GSPM_FWD2(T_, P_, F_, C_)                                                                        \
     hipLaunchKernelGGL((k_raster_fwd<T_, P_, F_, C_>), dim3(n_tiles), dim3(T_ * T_ / P_), 0, s, vt, rs, \
                        ranges, pair_vals, rec, rgb, depth, alpha, pointmap, t_final, last, contrib, visible,   \
                        order, tile_work, wmask, wstride, hdr)
 #define GSPM_FWD1(T_, P_, F_)                                                                  \
     do {                                                                                       \
-        if (rs.count_work) GSPM_FWD2(T_, P_, F_, true);                                        \
+        if (P_ == 1 && waves) GSPM_FWDW1(T_, F_);                                              \
+        else if (rs.count_work) GSPM_FWD2(T_, P_, F_, true);                                   \
         else GSPM_FWD2(T_, P_, F_, false);                                                     \
     } while (0)
 #define GSPM_FWD(T_, P_)                                      \
@@ -899,6 +1182,8 @@ hipError_t launch_raster_forward(const ViewTable &vt, const RasterSettings &rs, 
 #undef GSPM_FWD
 #undef GSPM_FWD2
 #undef GSPM_FWD1
+#undef GSPM_FWDW1
+#undef GSPM_FWDW
     return hipErrorInvalidValue;
 }
 
