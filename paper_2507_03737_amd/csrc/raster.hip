@@ -20,20 +20,20 @@
 //
 // The forward also records, per wave, which list entries one of its live pixels accepted
 // (one bit per entry and wave, kept in the frame state).  The backward walks only those
-// entries, front to back: in the matrix-core form each wave stages its own entries through
-// LDS, 32 at a time and with no workgroup barrier; otherwise the workgroup stages batches
-// of one record per lane.  It recomputes alpha and transmittance with the same
+// entries, front to back: with one pixel per lane by independent waves that stage their own
+// entries (k_raster_bwd_waves), otherwise by workgroups that stage batches of one record per
+// lane (k_raster_bwd).  It recomputes alpha and transmittance with the same
 // instructions as the forward, so no per-fragment state is stored: only the bits and the
 // per-pixel count of list entries up to the last contributing fragment.  The suffix sums
 // that the alpha derivative needs are carried as a remainder: it starts at the sum over
-// all fragments (from the forward's outputs) and each walked fragment subtracts its share.  Per record the wave needs up to 13
-// sums over its pixels: the moments of alpha dL/dalpha over the pixel offsets (from which
-// the mean, conic and opacity gradients follow) and the colour, depth and point sums.
-// With one pixel per lane these are a dense contraction (per-wave constant functions of
-// the pixel times per-record pixel values) done on the matrix cores for 8 records at a
-// time; with several pixels per lane each lane adds its pixels' contributions and the
-// wave adds them up with one reduce-scatter (cross-half lane swaps and DPP) of 8, 12 or
-// 16 values.  Either way the atomics are paid once per wave and record.
+// all fragments (from the forward's outputs) and each walked fragment subtracts its share.
+// Per record the wave needs up to 13 sums over its pixels: the moments of alpha dL/dalpha
+// over the pixel offsets (from which the mean, conic and opacity gradients follow) and the
+// colour, depth and point sums.  With one pixel per lane the wave forms them for 8 records
+// at a time, a lane per record and row of pixels; with several pixels per lane each lane
+// adds its pixels' contributions and the wave adds them up with one reduce-scatter
+// (cross-half lane swaps and DPP) of 8, 12 or 16 values.  Either way the atomics are paid
+// once per wave and record.
 #include <type_traits>
 
 #include "gspm_common.h"
@@ -679,51 +679,33 @@ struct BwdValues {
     static constexpr uint32_t kWColumns = (uint32_t)(kColumns >> (4 * (N - NW)));
 };
 
-template <int TILE, int PPT, bool POSE_ONLY, int FRAME, bool MX>
-__global__ void __launch_bounds__(TILE *TILE / PPT) __attribute__((amdgpu_waves_per_eu(MX && PPT == 1 ? 6 : 1)))
+// The frame state's layout follows the views, Gaussian count and tile of the call: unless they
+// (and the pointmap frame of the records) are the forward's, and the forward's lists are
+// complete, a backward may read nothing of it.  The test is uniform over the launch; one lane
+// records the refusal for gspm_frame_status.
+__device__ inline bool frame_matches(const ViewTable &vt, FrameHeader *hdr, int tile, int frame, int64_t n_records) {
+    if (hdr->magic != kFrameMagic || hdr->overflow != 0u || hdr->sort_stall != 0u || hdr->tile != (uint32_t)tile ||
+        hdr->n_views != (uint32_t)vt.n_views || hdr->n_tiles != (uint32_t)vt.tile_off[vt.n_views] ||
+        hdr->n_pixels != (uint64_t)vt.pix_off[vt.n_views] || hdr->n_records != (uint64_t)n_records ||
+        hdr->frame != (uint32_t)frame) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) hdr->bwd_error = 1u;
+        return false;
+    }
+    return true;
+}
+
+template <int TILE, int PPT, bool POSE_ONLY, int FRAME>
+__global__ void __launch_bounds__(TILE *TILE / PPT)
 k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, const uint32_t *__restrict__ vals,
              const float4 *__restrict__ rec, const uint32_t *__restrict__ last, const float *__restrict__ t_final,
              gspm_const_images fwd, gspm_const_images up, float *__restrict__ grad2d,
              const uint32_t *__restrict__ order, FrameHeader *__restrict__ hdr, int64_t n_records) {
-    // The frame state's layout follows the views, Gaussian count and tile of this call:
-    // unless they (and the pointmap frame of the records) are the forward's, and the
-    // forward's lists are complete, nothing below may be read.  The test is uniform over
-    // the launch; one lane records the refusal for gspm_frame_status.
-    if (hdr->magic != kFrameMagic || hdr->overflow != 0u || hdr->sort_stall != 0u || hdr->tile != (uint32_t)TILE ||
-        hdr->n_views != (uint32_t)vt.n_views || hdr->n_tiles != (uint32_t)vt.tile_off[vt.n_views] ||
-        hdr->n_pixels != (uint64_t)vt.pix_off[vt.n_views] || hdr->n_records != (uint64_t)n_records ||
-        hdr->frame != (uint32_t)FRAME) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) hdr->bwd_error = 1u;
-        return;
-    }
+    if (!frame_matches(vt, hdr, TILE, FRAME, n_records)) return;
     using L = Layout<TILE, PPT>;
     using V = BwdValues<POSE_ONLY, FRAME>;
     constexpr int NT = L::NT;
-    // One pixel per lane: the per-record sums are a dense contraction done on the matrix
-    // cores (below); each wave keeps its operand columns for kSlots records in LDS.
-    constexpr bool kMfma = MX && PPT == 1;
-    constexpr int kSlots = 8;
-    static_assert(!kMfma || (L::WW == 8 && L::WH == 8), "one pixel per lane means 8 x 8 wave rectangles");
-    // Records staged per batch for the whole workgroup; the matrix-core form stages per
-    // wave instead (kWS entries at a time), which with its operand buffers leaves room for
-    // six workgroups per compute unit (6 waves per SIMD, the register budget's target).
-    constexpr int NS = kMfma ? 1 : NT;
-    __shared__ float4 s0[NS], s1[NS], s2[NS], s3[NS];
-    constexpr int kWS = 32;  // entries a wave stages at a time (matrix-core form)
-    constexpr uint32_t kWSMask = kWS >= 32 ? 0xffffffffu : (uint32_t)((1ull << kWS) - 1ull);
-    __shared__ float4 mw0[kMfma ? L::NW : 1][kMfma ? kWS : 1], mw1[kMfma ? L::NW : 1][kMfma ? kWS : 1],
-        mw2[kMfma ? L::NW : 1][kMfma ? kWS : 1], mw3[kMfma ? L::NW : 1][kMfma ? kWS : 1];
+    __shared__ float4 s0[NT], s1[NT], s2[NT], s3[NT];
     __shared__ uint32_t block_last;
-    // B operand of slot column j (g: j = slot, w: j = 8 + slot) for pixel p = 4 kb + c
-    // (kb = 4 q + e): the 16-byte word 64 q + 16 c + (j ^ (c + 4 (q & 1))) holds the four
-    // pixels e = 0..3 of (q, c, j).  A flush lane's four values of one q are one 16-byte
-    // read, and the 16 lanes of each c read 16 consecutive words in a permuted order, which
-    // the LDS serves without conflicts; the XOR spreads the walk's one-column writes of the
-    // 64 pixels over all banks (measured: no conflict cycles either way, where the padded
-    // layout 272 q + 68 c + 4 j + e took 3.2 per read).
-    // Slot s's record (mean, index) follows at kMeta + 4 s: (u, v, -, index).
-    constexpr int kBq = 256, kBc = 64, kMeta = 4 * kBq;
-    __shared__ __align__(16) float mf_b[kMfma ? L::NW : 1][kMfma ? kMeta + 4 * kSlots : 4];
     const TilePos tp = tile_pos<TILE>(vt, order, blockIdx.x);
     const uint2 rg = ranges[tp.gt];
     const L lay;
@@ -791,115 +773,6 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
     __syncthreads();
     const uint32_t end = rg.x + block_last;
 
-    // Matrix-core form of the per-record sums (PPT = 1).  For records j of a wave and its
-    // 64 pixels p, every sum is  Out[f][j] = sum_p F_f(p) H_j(p):  the six moments take
-    // F = 1, x, y, x^2, xy, y^2 (pixel offsets from the wave rectangle's centre) and
-    // H = g = alpha dL/dalpha; the colour, depth and point sums take F = the pixel's
-    // upstream gradient and H = w = alpha T.  Out is 16 x 16 with rows f (6 moments, then
-    // up to 7 weighted sums) and columns (H in {g, w}) x (8 record slots), the contraction
-    // runs over the 64 pixels: 16 v_mfma_f32_16x16x4f32 per 8 records.  The A operand
-    // (F, 16 values per lane) is constant for the wave; the B operand (g and w of each
-    // slot) is written by the walk.  Lane L supplies A[L % 16][4 kb + L / 16] and
-    // B[4 kb + L / 16][L % 16] for step kb and receives D[4 (L / 16) + r][L % 16].
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = lane_id();
-    float Aop[kMfma ? 16 : 1];
-    // Byte offset of this lane's pixel in column 0 (bits 4-6 clear), with its word's XOR
-    // pattern in bits 4-6: column j's value then sits at (bofs ^ 16 j), one instruction
-    // per record.
-    const uint32_t bofs =
-        4u * (uint32_t)((wv * (kMeta + 4 * kSlots) + (lane >> 4) * kBq + (lane & 3) * kBc + ((lane >> 2) & 3)) |
-                        4 * ((lane & 3) + 4 * ((lane >> 4) & 1)));
-    int slot = 0;  // filled record slots of this wave (wave-uniform)
-    const float cxw = lay.rx0 + 3.5f, cyw = lay.ry0 + 3.5f;
-    if constexpr (kMfma) {
-        float *buf = mf_b[wv];
-        float wg[7];
-        int m = 0;
-        if (V::kColour) { wg[m++] = gC0[0]; wg[m++] = gC1[0]; wg[m++] = gC2[0]; }
-        if (V::kDepth) wg[m++] = gD[0];
-        if (V::kPoint) { wg[m++] = gX0[0]; wg[m++] = gX1[0]; wg[m++] = gX2[0]; }
-        // Pixel-major at a pitch of 9 words (coprime with the 32 banks): neither these writes
-        // nor the reads below meet bank conflicts.
-#pragma unroll
-        for (int t = 0; t < V::NW; ++t) buf[9 * lane + t] = wg[t];
-        __builtin_amdgcn_wave_barrier();
-        const int f = lane & 15, c = lane >> 4;
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb) {
-            const int p = 4 * kb + c;
-            const float x = (float)(p & 7) - 3.5f, y = (float)(p >> 3) - 3.5f;
-            float av = f == 0 ? 1.0f : f == 1 ? x : f == 2 ? y : f == 3 ? x * x : f == 4 ? x * y : y * y;
-            if (f >= 6) av = f < 6 + V::NW ? buf[9 * p + f - 6] : 0.0f;
-            Aop[kb] = av;
-        }
-        __builtin_amdgcn_wave_barrier();  // read before the walk overwrites the buffer
-    }
-    // What each lane of the flush produces: grad2d column j = lane % 16 of a record, from
-    // row f of B column (H, slot) of the product (src: its offset in the transposed block,
-    // has: the column is produced at all), and which moment it is (c1..c5: j = 1..5).
-    struct FlushLane {
-        bool has, c1, c2, c3, c4, c5;
-        int src;
-    } fl;
-    {
-        const int j = lane & 15;
-        int src_f = j <= 5 && (j > 0 || V::kOpacity) ? j : -1;
-#pragma unroll
-        for (int m = 0; m < V::NW; ++m)
-            if ((int)((V::kWColumns >> (4 * m)) & 15u) == j) src_f = 16 | (6 + m);
-        fl.has = src_f >= 0;
-        fl.src = fl.has ? (src_f >> 4) * 8 * 20 + (src_f & 15) : 0;
-        fl.c1 = j == 1; fl.c2 = j == 2; fl.c3 = j == 3; fl.c4 = j == 4; fl.c5 = j == 5;
-    }
-    // Contract the first n slots and add the results to the records' rows.
-    auto flush = [&](int n) {
-        __builtin_amdgcn_wave_barrier();  // the slots are written (a wave's LDS accesses stay in order)
-        const int j = lane & 15, c = lane >> 4;
-        const float *src0 = mf_b[wv] + kBc * c + 4 * (j ^ c);        // q = 0, 2
-        const float *src1 = mf_b[wv] + kBc * c + 4 * (j ^ (c + 4));  // q = 1, 3
-        const float4 q0 = *reinterpret_cast<const float4 *>(src0);
-        const float4 q1 = *reinterpret_cast<const float4 *>(src1 + kBq);
-        const float4 q2 = *reinterpret_cast<const float4 *>(src0 + 2 * kBq);
-        const float4 q3 = *reinterpret_cast<const float4 *>(src1 + 3 * kBq);
-        const float bq[16] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w,
-                              q2.x, q2.y, q2.z, q2.w, q3.x, q3.y, q3.z, q3.w};
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kb = 0; kb < 16; ++kb) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(Aop[kb], bq[kb], acc, 0, 0, 0);
-        // Transpose through LDS (over the B operand, read above) so that 16 adjacent lanes
-        // hold one record's row (one cache line per record and atomic instruction):
-        // dout[20 j + f] for column j, row f (the pitch of 20 keeps the 16-byte writes of a
-        // phase in distinct banks).
-        float *dout = mf_b[wv];
-        *reinterpret_cast<float4 *>(dout + j * 20 + 4 * c) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int sr = 4 * h + c;  // record slot of this lane
-            const float4 mt = *reinterpret_cast<const float4 *>(mf_b[wv] + kMeta + 4 * sr);
-            const float4 sm = *reinterpret_cast<const float4 *>(dout + sr * 20);  // S0, Sx, Sy, Sxx
-            const float val = fl.has ? dout[fl.src + sr * 20] : 0.0f;
-            // Moments about the wave centre -> about the record's mean (dx = x - ux):
-            // R_x = S_x - ux S0, R_xx = S_xx - 2 ux S_x + ux^2 S0, R_xy = S_xy - uy S_x -
-            // ux S_y + ux uy S0, and likewise in y.  The column of each lane picks its
-            // coefficients by selects on wave-constant lane masks (no branches).
-            const float ux = mt.x - cxw, uy = mt.y - cyw;
-            float al = fl.c1 ? -ux : 0.0f;
-            al = fl.c2 ? -uy : al;
-            al = fl.c3 ? ux * ux : al;
-            al = fl.c4 ? ux * uy : al;
-            al = fl.c5 ? uy * uy : al;
-            float be = fl.c3 ? -2.0f * ux : 0.0f;
-            be = fl.c4 ? -uy : be;
-            float ga = fl.c4 ? -ux : 0.0f;
-            ga = fl.c5 ? -2.0f * uy : ga;
-            const float out = fmaf(ga, sm.z, fmaf(be, sm.y, fmaf(al, sm.x, val)));
-            const uint32_t rid = __float_as_uint(mt.w);
-            if (sr < n && fl.has && out != 0.f) unsafeAtomicAdd(grad2d + (int64_t)rid * kG2 + j, out);
-        }
-        __builtin_amdgcn_wave_barrier();  // read before later records overwrite the buffer
-    };
-
     // The entries that one of this wave's live pixels accepted in the forward (its bit plane
     // after the pair list): every entry with a valid pixel here, plus the few that only
     // stopped a pixel, so the walk needs no culling test and meets almost no entry without
@@ -929,12 +802,6 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
             // Two comparisons whose lane masks are combined by a scalar AND.
             valid[k] = rel < my_last[k] && sq[k] <= b.y;
             any |= ballot(valid[k]);
-        }
-        if constexpr (kMfma) {
-            asm volatile("" ::"v"(cc.x), "v"(cc.y), "v"(cc.z), "v"(cc.w));
-            // Whole 16-byte reads (a 12-byte read of one address for the whole wave keeps the
-            // LDS busy twice as long).
-            if constexpr (V::kPoint) asm volatile("" ::"v"(d.x), "v"(d.y), "v"(d.z), "v"(d.w));
         }
         if (any == 0ull) return;  // wave-uniform
         float v[V::NR];
@@ -966,19 +833,6 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
                 const float dLda = T[k] * sv - Rem[k] * __builtin_amdgcn_rcpf(one_m);
                 const float g = kClamp && al >= amax ? 0.0f : dLda * al;
                 T[k] = fmaf(-al, T[k], T[k]);  // as in the forward
-                if constexpr (kMfma) {
-                    float *bw = reinterpret_cast<float *>(reinterpret_cast<char *>(&mf_b[0][0]) +
-                                                          (bofs ^ (16u * (uint32_t)slot)));
-                    bw[0] = g;
-                    bw[4 * kSlots] = w;
-                    // The slot's record mean and index, stored by lane 0 (whose pixel offset is
-                    // 0) behind the B operand, straight from the registers they were read into.
-                    if (lane == 0) {
-                        *reinterpret_cast<float2 *>(bw + kMeta) = make_float2(a.x, a.y);
-                        bw[kMeta + 3] = b.w;
-                    }
-                    continue;
-                }
                 const float gdx = g * dx, gdy = g * dy;
                 int t = 0;
                 if (V::kOpacity) add(t++, g);
@@ -1006,13 +860,6 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
         } else {
             pixel_terms(std::false_type{});
         }
-        if constexpr (kMfma) {
-            if (++slot == kSlots) {
-                flush(kSlots);
-                slot = 0;
-            }
-            return;
-        }
         int idx;
         const float tot = wave_reduce_scatter(v, idx);
         if (idx >= 0 && idx < V::N && tot != 0.f) {
@@ -1022,100 +869,375 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
             unsafeAtomicAdd(grad2d + (int64_t)r * kG2 + col, tot);
         }
     };
-    if constexpr (kMfma) {
-        // Each wave stages only the entries its bits mark, kWS at a time, in its own LDS
-        // area, and walks them with no workgroup barrier.  The entry's list position rides
-        // in the staged point's fourth component.
-        float4 *w0 = mw0[wv], *w1 = mw1[wv], *w2 = mw2[wv], *w3 = mw3[wv];
-        const uint32_t wend = rg.x + wave_last;
-        // The next 64 positions' bits and record indices are loaded one step ahead, so that
-        // a step waits on one global read (its records) rather than three dependent ones.
-        uint64_t m_next = 0ull;
-        uint32_t rec_next = 0u;
-        if (rg.x < wend) {
-            m_next = use_bits ? wave_bits(rg.x) : ~0ull;  // without bits every entry is tested
-            rec_next = rg.x + (uint32_t)lane < wend ? vals[rg.x + (uint32_t)lane] : 0u;
-        }
-        for (uint32_t pos = rg.x; pos < wend; pos += kWave) {
-            uint64_t m = m_next;
-            const uint32_t rec_here = rec_next;
-            const uint32_t np = pos + (uint32_t)kWave;
-            if (np < wend) {
-                m_next = use_bits ? wave_bits(np) : ~0ull;
-                rec_next = np + (uint32_t)lane < wend ? vals[np + (uint32_t)lane] : 0u;
+    // The next batch's record indices are loaded one batch ahead, so staging waits on one
+    // global read (the record) rather than two dependent ones.
+    uint32_t vnext = (rg.x + threadIdx.x < end) ? vals[rg.x + threadIdx.x] : 0u;
+    for (uint32_t base = rg.x; base < end; base += NT) {
+        const uint32_t kk = base + threadIdx.x;
+        const uint32_t vcur = vnext;
+        if (kk + NT < end) vnext = vals[kk + NT];
+        const uint64_t bits0 = use_bits ? wave_bits(base) : 0ull;  // read while the batch is staged
+        if (kk < end) stage(rec, vcur, tp.x0, tp.y0, s0, s1, s2, s3, threadIdx.x);
+        __syncthreads();
+        const int cnt = (int)min((uint32_t)NT, end - base);
+        const uint32_t rel0 = base - rg.x;
+        for (int c = 0; c < cnt && rel0 + (uint32_t)c < wave_last; c += kWave) {
+            uint64_t m;
+            if (use_bits) {
+                m = c == 0 ? bits0 : wave_bits(base + (uint32_t)c);
+                if (cnt - c < kWave) m &= (1ull << (cnt - c)) - 1ull;  // the next tile's entries
+            } else {
+                m = batch_mask<L::CULL>(s0, s1, c, cnt, lay.rx0, lay.rx1, lay.ry0, lay.ry1);
             }
-            const uint32_t lim = wend - pos;
+            // Entries at or past the wave's last contributing one are not walked.
+            const uint32_t lim = wave_last - (rel0 + (uint32_t)c);
             if (lim < (uint32_t)kWave) m &= (1ull << lim) - 1ull;
-            // Lane L holds the record index of position pos + L.
-            const bool mine = (m >> lane) & 1ull;
-            const uint32_t my_rec = rec_here;
-#pragma unroll
-            for (int h = 0; h < kWave / kWS; ++h) {
-                const uint32_t mh = (uint32_t)((m >> (kWS * h)) & kWSMask);
-                if (mh == 0u) continue;  // wave-uniform
-                const int sub = lane - kWS * h;  // this lane's bit within the half
-                if (mine && sub >= 0 && sub < kWS) {
-                    const uint32_t si = (uint32_t)__popc(mh & ((1u << sub) - 1u));
-                    const uint32_t p = pos + (uint32_t)lane;
-                    const uint32_t rel = p - rg.x;
-                    stage(rec, my_rec, tp.x0, tp.y0, w0, w1, w2, w3, (int)si, &rel);
-                }
-                __builtin_amdgcn_wave_barrier();  // staged (a wave's LDS accesses stay in order)
-                const int n_st = __popc(mh);
-                for (int i = 0; i < n_st; ++i) {
-                    const float4 a = w0[i];
-                    const float4 b = w1[i];
-                    const float4 cc = w2[i];
-                    const float4 d = w3[i];
-                    // One 16-byte read now rather than a second, split read after the test.
-                    asm volatile("" ::"v"(b.z), "v"(b.w));
-                    walk_record(a, b, cc, d, __float_as_uint(d.w));
-                }
-                __builtin_amdgcn_wave_barrier();  // read before the next entries are staged
+            while (m != 0ull) {
+                const int q = c + (int)__builtin_ctzll(m);
+                m &= m - 1ull;
+                const uint32_t rel = rel0 + (uint32_t)q;
+                const float4 a = s0[q];
+                const float4 b = s1[q];
+                const float4 cc = s2[q];
+                const float4 d = s3[q];
+                // One 16-byte read now rather than a second, split read after the test.
+                asm volatile("" ::"v"(b.z), "v"(b.w));
+                walk_record(a, b, cc, d, rel);
             }
         }
-    } else {
-        // The next batch's record indices are loaded one batch ahead, so staging waits on one
-        // global read (the record) rather than two dependent ones.
-        uint32_t vnext = (threadIdx.x < NS && rg.x + threadIdx.x < end) ? vals[rg.x + threadIdx.x] : 0u;
-        for (uint32_t base = rg.x; base < end; base += NS) {
-            const uint32_t kk = base + threadIdx.x;
-            const uint32_t vcur = vnext;
-            if (threadIdx.x < NS && kk + NS < end) vnext = vals[kk + NS];
-            const uint64_t bits0 = use_bits ? wave_bits(base) : 0ull;  // read while the batch is staged
-            if (threadIdx.x < NS && kk < end) stage(rec, vcur, tp.x0, tp.y0, s0, s1, s2, s3, threadIdx.x);
-            __syncthreads();
-            const int cnt = (int)min((uint32_t)NS, end - base);
-            const uint32_t rel0 = base - rg.x;
-            for (int c = 0; c < cnt && rel0 + (uint32_t)c < wave_last; c += kWave) {
-                uint64_t m;
-                if (use_bits) {
-                    m = c == 0 ? bits0 : wave_bits(base + (uint32_t)c);
-                    if (cnt - c < kWave) m &= (1ull << (cnt - c)) - 1ull;  // the next tile's entries
-                } else {
-                    m = batch_mask<L::CULL>(s0, s1, c, cnt, lay.rx0, lay.rx1, lay.ry0, lay.ry1);
-                }
-                // Entries at or past the wave's last contributing one are not walked.
-                const uint32_t lim = wave_last - (rel0 + (uint32_t)c);
-                if (lim < (uint32_t)kWave) m &= (1ull << lim) - 1ull;
-                while (m != 0ull) {
-                    const int q = c + (int)__builtin_ctzll(m);
-                    m &= m - 1ull;
-                    const uint32_t rel = rel0 + (uint32_t)q;
-                    const float4 a = s0[q];
-                    const float4 b = s1[q];
-                    const float4 cc = s2[q];
-                    const float4 d = s3[q];
-                    // One 16-byte read now rather than a second, split read after the test.
-                    asm volatile("" ::"v"(b.z), "v"(b.w));
-                    walk_record(a, b, cc, d, rel);
-                }
-            }
-            __syncthreads();
-        }
+        __syncthreads();
     }
-    if constexpr (kMfma) {
-        if (slot > 0) flush(slot);  // wave-uniform
+}
+
+constexpr int kBatch = 16;          // entries staged at a time: four lanes load one record
+constexpr int kBatchPlane = kBatch + 2;  // words of a staging plane: quad-lane writes without bank conflicts
+constexpr int kQueue = 128;         // ring of entries waiting to be staged: at most 15 + 64
+constexpr int kSlots = 8;           // entries whose pixel values are summed together
+constexpr int kPart = 13;           // columns of grad2d that a slot's partial sums fill
+
+// Backward compositing, one pixel per lane, by independent waves.
+//
+// A wave stages the entries its bits mark 16 at a time (loaded one batch ahead) and walks them
+// four at a time, so that their LDS reads and exponents overlap; only the transmittance and
+// the remainder pass from one entry to the next, and one reciprocal serves the four.
+//
+// Per entry the wave needs up to 13 sums over its 64 pixels: Out[f] = sum_p F_f(p) H(p), where
+// the six moments take F = 1, x, y, x^2, xy, y^2 (pixel offsets from the wave rectangle's
+// centre) and H = g = alpha dL/dalpha, and the colour, depth and point sums take F = the
+// pixel's upstream gradient and H = w = alpha T.  Every eight entries, g and w pass through LDS
+// so that lane 8 r + y holds row y of entry r's 8 x 8 pixels: three row moments (the x offsets
+// are constants, paired about the centre) and the weighted sums over 8 pixels whose upstream
+// gradients the lane keeps in registers; the y moments are products of these.  The 8 rows'
+// partial sums pass through LDS once more to 16 lanes per entry, which add, re-centre and store
+// them.  (As a product on the matrix cores this is no faster: f32 matrix instructions run at
+// the rate of vector ones, 32 multiply-adds per cycle, never beside them, and the 16x16x4 and
+// 4x4x1 shapes spend half and a quarter of it on rows and columns that are not needed.)
+//
+// Vector issue (about 46 instructions per entry and wave) and the LDS (29 cycles per entry, two
+// thirds of its time) bind it together.  8 views with 1M Gaussians: 1.43 ms before (workgroups,
+// entries one by one, 16x16x4 products), 1.09 ms now; pose-only at 960x640 with 500k: 274 and
+// 190 us.  Four waves per SIMD fit the registers without spilling; five are slower.
+template <int TILE, bool POSE_ONLY, int FRAME>
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
+k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges,
+                   const uint32_t *__restrict__ vals, const float4 *__restrict__ rec,
+                   const uint32_t *__restrict__ last, const float *__restrict__ t_final, gspm_const_images fwd,
+                   gspm_const_images up, float *__restrict__ grad2d, const uint32_t *__restrict__ order,
+                   FrameHeader *__restrict__ hdr, int64_t n_records) {
+    if (!frame_matches(vt, hdr, TILE, FRAME, n_records)) return;
+    using L = Layout<TILE, 1>;
+    using V = BwdValues<POSE_ONLY, FRAME>;
+    static_assert(L::WW == 8 && L::WH == 8, "8 x 8 wave rectangles");
+    // Staged entries: (u, v, a, b), (c, threshold, opacity, list position), colour and z, point
+    // and record index.
+    __shared__ float4 st[4 * kBatchPlane];
+    __shared__ uint2 queue[kQueue];  // (record, list position) of the marked entries
+    // The slots' g and w (H = 0, 1): the value of slot r at pixel (x, y), x = 4 h + e, is
+    // element e of word 128 H + 16 r + 8 (h ^ (r & 1)) + (y ^ 4 h).  The 16 lanes of two slots
+    // read 16 different words mod 16, 32 pixels' writes fall into 32 banks, and a slot's
+    // place is a constant offset.  Then, over the same words, the partial sums: float
+    // [slot][y / 4][column][y % 4], the slots 104 and the halves 52 floats apart (8 and 20 mod
+    // 32: writes and 16-byte reads without bank conflicts).
+    __shared__ float4 gw[2 * 16 * kSlots];
+    static_assert(kSlots * kPart * 8 <= 4 * 2 * 16 * kSlots, "the partial sums fit");
+    uint32_t tslot;
+    int wv;
+    wave_place<L::NW>(blockIdx.x, tslot, wv);
+    if (tslot >= (uint32_t)vt.tile_off[vt.n_views]) return;
+    const TilePos tp = tile_pos<TILE>(vt, order, tslot);
+    const uint2 rg = ranges[tp.gt];
+    const L lay(wv);
+    const int lane = lane_id();
+    const float px = (float)lay.lx, py = (float)lay.ly, amax = rs.alpha_max;
+    const int i = tp.tx * TILE + lay.lx, j = tp.ty * TILE + lay.ly;
+    // The pixel's upstream gradient and, to start the walk's remainder Rem, the total
+    // G = sum_k w_k (g . e_k) + T_final (g_C . bg) that the forward's outputs give.
+    uint32_t my_last = 0u;
+    float gC0 = 0.f, gC1 = 0.f, gC2 = 0.f, gD = 0.f, gA = 0.f, gX0 = 0.f, gX1 = 0.f, gX2 = 0.f, Rem = 0.f, T = 1.0f;
+    if (i < tp.W && j < tp.H) {
+        const int64_t e = (int64_t)j * tp.W + i;
+        const int64_t pix = tp.pix_off + e, o3 = 3 * tp.pix_off + e, plane = tp.plane;
+        my_last = last[pix];
+        gC0 = load_or0(up.rgb, o3);
+        gC1 = load_or0(up.rgb, o3 + plane);
+        gC2 = load_or0(up.rgb, o3 + 2 * plane);
+        gD = load_or0(up.depth, pix);
+        gA = load_or0(up.alpha, pix);
+        gX0 = load_or0(up.pointmap, o3);
+        gX1 = load_or0(up.pointmap, o3 + plane);
+        gX2 = load_or0(up.pointmap, o3 + 2 * plane);
+        const float Tf = t_final[pix];
+        const bool none = gC0 == 0.f && gC1 == 0.f && gC2 == 0.f && gD == 0.f && gA == 0.f && gX0 == 0.f &&
+                          gX1 == 0.f && gX2 == 0.f;
+        // The rgb output holds sum_k w_k c_k + T_final bg, which is exactly what G needs.
+        Rem = gC0 * fwd.rgb[o3] + gC1 * fwd.rgb[o3 + plane] + gC2 * fwd.rgb[o3 + 2 * plane] + gD * fwd.depth[pix] +
+              gA * (1.0f - Tf);
+        if (FRAME == 2) {
+            // Eq. 5: the pointmap is D K^-1 [i, j, 1]^T, a function of the depth only.
+            const float rx = ((float)i - vt.cx[tp.v]) / vt.fx[tp.v];
+            const float ry = ((float)j - vt.cy[tp.v]) / vt.fy[tp.v];
+            const float gXD = gX0 * rx + gX1 * ry + gX2;
+            Rem += gXD * fwd.depth[pix];
+            gD += gXD;
+            gX0 = gX1 = gX2 = 0.f;
+        } else {
+            Rem += gX0 * fwd.pointmap[o3] + gX1 * fwd.pointmap[o3 + plane] + gX2 * fwd.pointmap[o3 + 2 * plane];
+        }
+        if (FRAME == 1) {
+            // The depth is the point's z: one gradient for both.
+            gX2 += gD;
+            gD = 0.f;
+        }
+        if (none) my_last = 0u;  // nothing flows back from this pixel
+    }
+    uint32_t wave_last = my_last;
+    for (int off = 32; off > 0; off >>= 1) wave_last = max(wave_last, (uint32_t)__shfl_xor((int)wave_last, off, 64));
+    wave_last = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_last);  // uniform: keep it scalar
+    if (wave_last == 0u) return;
+
+    float *gwf = reinterpret_cast<float *>(gw);
+    // The upstream gradients of the flush lane's row of pixels, y = lane % 8.
+    const int slot = lane >> 3, y = lane & 7;
+    float U[V::NW][8];
+    {
+        float wg[7];
+        int m = 0;
+        if (V::kColour) { wg[m++] = gC0; wg[m++] = gC1; wg[m++] = gC2; }
+        if (V::kDepth) wg[m++] = gD;
+        if (V::kPoint) { wg[m++] = gX0; wg[m++] = gX1; wg[m++] = gX2; }
+#pragma unroll
+        for (int t = 0; t < V::NW; ++t) gwf[64 * t + lane] = wg[t];
+        wave_sync();
+#pragma unroll
+        for (int t = 0; t < V::NW; ++t)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) U[t][k] = gwf[64 * t + 8 * y + k];
+        wave_sync();  // read before the walk overwrites the buffer
+    }
+    // This pixel's place in gw (floats) for even and odd slots, less 64 per slot.
+    const int ph = (lane >> 2) & 1, pw = 4 * ((lane >> 3) ^ (4 * ph)) + (lane & 3);
+    const int at[2] = {32 * ph + pw, 32 * (ph ^ 1) + pw};
+    // The flush lane's words of its row's left half (the right half's is 8 ^ 4 away by XOR).
+    const int rd = 16 * slot + 8 * (slot & 1) + y;
+    const float yc = (float)y - 3.5f;
+    // What each lane adds after that: column col of entry lane / 16 (+ 4), and the constants of
+    // its recentring.
+    const int col = lane & 15;
+    bool has = col <= 5 && (col > 0 || V::kOpacity);
+#pragma unroll
+    for (int m = 0; m < V::NW; ++m) has = has || (int)((V::kWColumns >> (4 * m)) & 15u) == col;
+    const float kx = col == 1 || col == 3 || col == 4 ? 1.0f : 0.0f, ky = col == 2 || col == 5 ? 1.0f : 0.0f;
+    const float lx = col == 3 ? 1.0f : 0.0f, ly = col == 4 || col == 5 ? 1.0f : 0.0f;
+    const float l1 = col == 1 || col == 2 ? -1.0f : 0.0f;
+    const float bx = col == 3 ? -2.0f : 0.0f, by = col == 4 ? -1.0f : 0.0f;
+    const float gx = col == 4 ? -1.0f : 0.0f, gy = col == 5 ? -2.0f : 0.0f;
+    const float cxw = lay.rx0 + 3.5f, cyw = lay.ry0 + 3.5f;
+    // Adds the sums of the n <= 8 entries staged from slot g on.
+    auto flush = [&](int g, int n) {
+        wave_sync();
+        const float4 ga = gw[rd], gb = gw[rd ^ 12], wa = gw[128 + rd], wb = gw[128 + (rd ^ 12)];
+        float part[6];
+        {
+            // x = -3.5 .. 3.5: sums and differences of the pixels paired about the centre.
+            const float p0 = gb.w + ga.x, p1 = gb.z + ga.y, p2 = gb.y + ga.z, p3 = gb.x + ga.w;
+            const float m0 = gb.w - ga.x, m1 = gb.z - ga.y, m2 = gb.y - ga.z, m3 = gb.x - ga.w;
+            const float s0 = (p0 + p1) + (p2 + p3);
+            const float s1 = fmaf(3.5f, m0, fmaf(2.5f, m1, fmaf(1.5f, m2, 0.5f * m3)));
+            const float s2 = fmaf(12.25f, p0, fmaf(6.25f, p1, fmaf(2.25f, p2, 0.25f * p3)));
+            const float sy = yc * s0;
+            part[0] = s0;
+            part[1] = s1;
+            part[2] = sy;
+            part[3] = s2;
+            part[4] = yc * s1;
+            part[5] = yc * sy;
+        }
+        float *dst = gwf + 8 * kPart * slot + 4 * kPart * (y >> 2) + (y & 3);
+        wave_sync();  // g and w have been read
+#pragma unroll
+        for (int c = 0; c < 6; ++c) dst[4 * c] = part[c];
+#pragma unroll
+        for (int m = 0; m < V::NW; ++m) {
+            const float *u = U[m];
+            const float v = fmaf(wa.x, u[0], fmaf(wa.y, u[1], fmaf(wa.z, u[2], wa.w * u[3]))) +
+                            fmaf(wb.x, u[4], fmaf(wb.y, u[5], fmaf(wb.z, u[6], wb.w * u[7])));
+            dst[4 * ((V::kWColumns >> (4 * m)) & 15u)] = v;
+        }
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = 4 * h + (lane >> 4);  // entry of this lane: 16 adjacent lanes hold one row
+            const float4 *src = gw + 2 * kPart * e + col;
+            const float4 a = src[0], b = src[kPart];
+            const float2 mean = *reinterpret_cast<const float2 *>(&st[g + e]);
+            const uint32_t rid = __float_as_uint(st[3 * kBatchPlane + g + e].w);
+            asm volatile("" ::"v"(rid));  // read before the branch
+            const float val = ((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w));
+            // Moments about the wave centre -> about the record's mean (dx = x - ux):
+            // R_x = S_x - ux S0, R_xx = S_xx - 2 ux S_x + ux^2 S0, R_xy = S_xy - uy S_x -
+            // ux S_y + ux uy S0, and likewise in y, with each column's coefficients picked by
+            // products with lane constants (exact: 0, +-1, -2).
+            const float S0 = GSPM_DPP_MOV(val, 0x150), Sx = GSPM_DPP_MOV(val, 0x151), Sy = GSPM_DPP_MOV(val, 0x152);  // row_newbcast
+            const float ux = mean.x - cxw, uy = mean.y - cyw;
+            const float al = fmaf(kx, ux, ky * uy) * fmaf(lx, ux, fmaf(ly, uy, l1));
+            const float be = fmaf(bx, ux, by * uy), ga2 = fmaf(gx, ux, gy * uy);
+            const float out = fmaf(ga2, Sy, fmaf(be, Sx, fmaf(al, S0, val)));
+            if (e < n && has && out != 0.f) unsafeAtomicAdd(grad2d + (int64_t)rid * kG2 + col, out);
+        }
+        wave_sync();  // read before the next entries overwrite the buffer
+    };
+
+    // The entries that one of this wave's live pixels accepted in the forward (its bit plane
+    // after the pair list): every entry with a valid pixel here, plus the few that only
+    // stopped a pixel, so the walk needs no culling test.
+    const int64_t cap = (int64_t)hdr->capacity;
+    const uint64_t *plane = wmask_at(vals, cap) + (int64_t)wv * wmask_stride(cap);
+    // A forward with another number of pixels per lane had other waves: every entry is tested.
+    const bool use_bits = hdr->ppt == 1u;
+    auto wave_bits = [&](uint32_t pos) {  // the 64 bits of list positions pos .. pos + 63
+        const uint64_t *wp = plane + (pos >> 6);
+        const int sh = (int)(pos & 63u);
+        uint64_t m = wp[0] >> sh;
+        if (sh != 0) m |= wp[1] << (64 - sh);
+        return m;
+    };
+    // The next 64 positions' bits and record indices are loaded one step ahead.
+    const uint32_t wend = rg.x + wave_last;
+    uint32_t pos = rg.x, head = 0u, tail = 0u;
+    uint64_t m_next = 0ull;
+    uint32_t rec_next = 0u;
+    auto load_step = [&]() {
+        m_next = use_bits ? wave_bits(pos) : ~0ull;
+        if (wend - pos < (uint32_t)kWave) m_next &= (1ull << (wend - pos)) - 1ull;
+        rec_next = pos + (uint32_t)lane < wend ? vals[pos + (uint32_t)lane] : 0u;
+    };
+    load_step();
+    // Queues marked entries until a batch is complete or the list ends.
+    auto fill = [&]() {
+        while (tail - head < (uint32_t)kBatch && pos < wend) {
+            const uint64_t m = m_next;
+            const uint32_t r = rec_next, rel = pos - rg.x + (uint32_t)lane;
+            pos += kWave;
+            if (pos < wend) load_step();
+            if ((m >> lane) & 1ull) {
+                const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                queue[(tail + rank) % kQueue] = make_uint2(r, rel);
+            }
+            tail += (uint32_t)__popcll(m);
+        }
+        wave_sync();
+    };
+    // Lane 4 e + w loads word w of the batch's entry e.
+    uint32_t cnt = 0u;
+    uint2 mine;
+    v4f word;
+    auto load_batch = [&]() {
+        cnt = min((uint32_t)kBatch, tail - head);
+        const uint32_t e = min((uint32_t)lane >> 2, cnt - 1u);
+        mine = queue[(head + e) % kQueue];
+        word = reinterpret_cast<const v4f *>(rec)[4 * (int64_t)mine.x + (lane & 3)];
+        head += cnt;
+    };
+    fill();
+    if (tail != head) load_batch();
+    while (cnt != 0u) {
+        // Stage the batch: word 0 takes the conic's (a, b) from its quad neighbour, word 1 the
+        // threshold of word 3; slots past the batch's end accept nothing.
+        const uint32_t n = cnt;
+        bool clampy;
+        {
+            const int w = lane & 3;
+            const bool dead = (uint32_t)lane >> 2 >= n;
+            float4 o = make_float4(word.x, word.y, word.z, word.w);
+            const float ca = GSPM_DPP_MOV(o.x, 0x55), cb = GSPM_DPP_MOV(o.y, 0x55);  // lane 1 of the quad
+            const float thr = GSPM_DPP_MOV(o.w, 0xff);                               // lane 3
+            if (w == 0) o = make_float4((word.x - tp.x0) + word.z, (word.y - tp.y0) + word.w, ca, cb);
+            if (w == 1) o = make_float4(word.z, dead ? -__builtin_inff() : thr, word.w, __uint_as_float(mine.y));
+            if (w == 3) o.w = __uint_as_float(mine.x);
+            clampy = ballot(w == 1 && word.w >= amax) != 0ull;
+            wave_sync();  // the previous batch has been read
+            st[w * kBatchPlane + (lane >> 2)] = o;
+        }
+        fill();
+        cnt = 0u;
+        if (tail != head) load_batch();
+        auto walk = [&](auto may_clamp) {
+            constexpr bool kClamp = decltype(may_clamp)::value;
+            for (uint32_t g = 0u; g < n; g += 4u) {
+                float al[4], sv[4], w[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float4 a = st[g + t], b = st[kBatchPlane + g + t], c = st[2 * kBatchPlane + g + t];
+                    // Whole 16-byte reads where three words are used (a 12-byte read keeps the
+                    // LDS busy twice as long, an 8-byte one half as long).  In the camera
+                    // frame the point's z is the depth, the colour's fourth word.
+                    asm volatile("" ::"v"(c.w));
+                    sv[t] = fmaf(gC0, c.x, fmaf(gC1, c.y, fmaf(gC2, c.z, gA)));
+                    if (V::kDepth) sv[t] = fmaf(gD, c.w, sv[t]);
+                    if (FRAME == 1) {
+                        const float2 d = *reinterpret_cast<const float2 *>(&st[3 * kBatchPlane + g + t]);
+                        sv[t] = fmaf(gX0, d.x, fmaf(gX1, d.y, fmaf(gX2, c.w, sv[t])));
+                    }
+                    if (FRAME == 0) {
+                        const float4 d = st[3 * kBatchPlane + g + t];
+                        asm volatile("" ::"v"(d.w));
+                        sv[t] = fmaf(gX0, d.x, fmaf(gX1, d.y, fmaf(gX2, d.z, sv[t])));
+                    }
+                    const float dx = px - a.x;
+                    const float sq = quad_s(a.z * dx, a.w, b.x, py - a.y);
+                    const uint64_t valid = ballot(sq <= b.y) & ballot(__float_as_uint(b.w) < my_last);
+                    float ao = b.z * __builtin_amdgcn_exp2f(-sq);
+                    if (kClamp) ao = clamp_alpha(ao, amax);
+                    // An invalid pixel takes alpha = 0: no weight, no gradient, T unchanged.
+                    al[t] = in_mask(valid) ? ao : 0.0f;
+                }
+                // Front to back: the weights, and Rem = G - sum of w s over these and earlier
+                // fragments: the later fragments' share plus the background term.
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    w[t] = __fmul_rn(al[t], T);
+                    Rem = fmaf(-w[t], sv[t], Rem);
+                    T = fmaf(-al[t], T, T);  // as in the forward
+                }
+                // Back to front over the group: with Q = Rem / T behind a fragment (what the later
+                // fragments and the background would show), alpha dL/dalpha = w (s - Q) and
+                // Q in front of it = Q + alpha (s - Q): one reciprocal per group.  (A T below the
+                // bound has weights far below rounding; its reciprocal might not be finite.)
+                float Q = Rem * __builtin_amdgcn_rcpf(fmaxf(T, 0x1p-100f));
+                float *dst = gwf + 64 * (g & 4u);
+#pragma unroll
+                for (int t = 3; t >= 0; --t) {
+                    const float d = sv[t] - Q;
+                    Q = fmaf(al[t], d, Q);
+                    // A clamped alpha passes no gradient.
+                    dst[at[t & 1] + 64 * t] = kClamp && al[t] >= amax ? 0.0f : w[t] * d;
+                    dst[at[t & 1] + 64 * t + 512] = w[t];
+                }
+                if ((g & 4u) != 0u || g + 4u >= n) flush((int)(g & ~7u), (int)min(8u, n - (g & ~7u)));
+            }
+        };
+        if (clampy) walk(std::true_type{});
+        else walk(std::false_type{});
     }
 }
 
@@ -1195,33 +1317,31 @@ hipError_t launch_raster_backward(const ViewTable &vt, const RasterSettings &rs,
     const int n_tiles = vt.tile_off[vt.n_views];
     const float4 *rec = reinterpret_cast<const float4 *>(records);
     if (rs.frame < 0 || rs.frame > 2) return hipErrorInvalidValue;
-#define GSPM_BWD1(T_, P_, PO_, F_, MX_)                                                                         \
-    hipLaunchKernelGGL((k_raster_bwd<T_, P_, PO_, F_, MX_>), dim3(n_tiles), dim3(T_ * T_ / P_), 0, s, vt, rs, \
-                       ranges, pair_vals, rec, last, t_final, fwd, up, grad2d, order, hdr, n_records)
-#define GSPM_BWD2(T_, P_, PO_, MX_)                            \
-    if (rs.frame == 0) GSPM_BWD1(T_, P_, PO_, 0, MX_);         \
-    else if (rs.frame == 1) GSPM_BWD1(T_, P_, PO_, 1, MX_);    \
-    else GSPM_BWD1(T_, P_, PO_, 2, MX_);
-    // The matrix-core form exists at one pixel per lane only (MX = false elsewhere, so no
-    // kernel is instantiated twice).
-#define GSPM_BWD3(T_, P_, PO_)                                 \
-    if (!rs.bwd_lane_reduce) {                                 \
-        GSPM_BWD2(T_, P_, PO_, (P_ == 1))                      \
-    } else {                                                   \
-        GSPM_BWD2(T_, P_, PO_, false)                          \
-    }
+#define GSPM_BWD1(T_, P_, PO_, F_)                                                                          \
+    do {                                                                                                    \
+        if (P_ == 1 && !rs.bwd_lane_reduce)                                                                 \
+            hipLaunchKernelGGL((k_raster_bwd_waves<T_, PO_, F_>), dim3(wave_grid<Layout<T_, 1>::NW>(n_tiles)),  \
+                               dim3(kWave), 0, s, vt, rs, ranges, pair_vals, rec, last, t_final, fwd, up,    \
+                               grad2d, order, hdr, n_records);                                              \
+        else                                                                                                \
+            hipLaunchKernelGGL((k_raster_bwd<T_, P_, PO_, F_>), dim3(n_tiles), dim3(T_ * T_ / P_), 0, s, vt, rs, \
+                               ranges, pair_vals, rec, last, t_final, fwd, up, grad2d, order, hdr, n_records);  \
+    } while (0)
+#define GSPM_BWD2(T_, P_, PO_)                        \
+    if (rs.frame == 0) GSPM_BWD1(T_, P_, PO_, 0);     \
+    else if (rs.frame == 1) GSPM_BWD1(T_, P_, PO_, 1);\
+    else GSPM_BWD1(T_, P_, PO_, 2);
 #define GSPM_BWD(T_, P_)                                  \
     if (vt.tile == T_ && vt.ppt == P_) {                  \
         if (pose_only) {                                  \
-            GSPM_BWD3(T_, P_, true)                       \
+            GSPM_BWD2(T_, P_, true)                       \
         } else {                                          \
-            GSPM_BWD3(T_, P_, false)                      \
+            GSPM_BWD2(T_, P_, false)                      \
         }                                                 \
         return hipGetLastError();                         \
     }
     GSPM_RASTER_CONFIGS(GSPM_BWD)
 #undef GSPM_BWD
-#undef GSPM_BWD3
 #undef GSPM_BWD2
 #undef GSPM_BWD1
     return hipErrorInvalidValue;
