@@ -397,7 +397,8 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
         //    depth (stable, so ties keep record order).
         PhaseTimer t_ds(ctx, hs, GSPM_PHASE_DEPTH_SORT);
         GSPM_HIP(launch_compact(counts, static_cast<uint32_t *>(ctx->dkey.p), R, static_cast<uint32_t *>(ctx->dval.p),
-                                static_cast<uint32_t *>(ctx->live.p), n_live, part, pack, hs));
+                                static_cast<uint32_t *>(ctx->live.p), n_live, part, pack, hist, radix_total_words(db),
+                                hs));
         GSPM_HIP(radix_sort(static_cast<uint32_t *>(ctx->dval.p), static_cast<uint32_t *>(ctx->live.p),
                             static_cast<uint32_t *>(ctx->dkey_tmp.p), static_cast<uint32_t *>(ctx->dval_tmp.p),
                             static_cast<uint32_t *>(ctx->dkey_s.p), static_cast<uint32_t *>(ctx->dval_s.p), R, n_live,
@@ -425,7 +426,8 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
                            records, static_cast<const uint4 *>(ctx->spans.p), P.rs, R, g->n > 0 ? g->n : 1, P.vt,
                            static_cast<uint32_t *>(ctx->pkey.p),
                            static_cast<uint32_t *>(ctx->pval.p), hdr, (uint32_t)cap, total,
-                           static_cast<uint32_t *>(ctx->big.p), total + 1, n_live, ranges, twork, P.n_tiles, hs));
+                           static_cast<uint32_t *>(ctx->big.p), total + 1, n_live, ranges, twork, P.n_tiles, hist,
+                           radix_total_words(db), hs));
     t_bin.stop();
     // 5. Stable sort by tile id; its final pass writes the per-tile ranges (6).
     if (cap > 0) {

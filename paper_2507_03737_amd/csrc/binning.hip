@@ -7,6 +7,8 @@
 // (depth, record index) without ever carrying depth bits in the large pair sort.  The
 // pair count is only known on the device: all kernels after the scan read it from
 // device memory and use fixed grids, so the whole sequence can be captured in a graph.
+#include <algorithm>
+
 #include "gspm_common.h"
 
 namespace gspm {
@@ -63,8 +65,12 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t x, uint32_t *lds, uint3
 
 __global__ void __launch_bounds__(kScanBlock)
 k_scan_reduce(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ idx, const uint32_t *__restrict__ n_dev,
-              int64_t n_max, int flag, uint32_t *__restrict__ part, uint32_t *__restrict__ gathered) {
+              int64_t n_max, int flag, uint32_t *__restrict__ part, uint32_t *__restrict__ gathered,
+              uint32_t *__restrict__ clear, int n_clear) {
     __shared__ uint32_t lds[kScanBlock / kWave];
+    // Words that a later kernel adds to, cleared here to save a launch.
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < n_clear; i += kScanBlock) clear[i] = 0u;
     const int64_t n = scan_n(n_dev, n_max);
     const int64_t chunk = scan_chunk(n);
     const int64_t b0 = (int64_t)blockIdx.x * chunk < n ? (int64_t)blockIdx.x * chunk : n;
@@ -228,7 +234,7 @@ k_scan_compact(const uint32_t *__restrict__ counts, const uint32_t *__restrict__
 // LSD radix sort with one histogram pass for every digit and one kernel per digit pass
 // (the single-sweep scheme with decoupled look-back of Merrill and Garland's scan and
 // Adinets and Merrill's Onesweep sort).  Keys are cut into tiles of 8192 (8 waves x 16
-// steps of 64).  Block b of a pass kernel ranks tile b's keys stably (wave-level match of
+// steps of 64; fewer steps for small sorts, below).  Block b of a pass kernel ranks tile b's keys stably (wave-level match of
 // equal digits by ballots, then per-digit offsets across the eight waves).  In the first
 // pass the count of each digit in all earlier tiles comes from the histogram kernel,
 // which counts the first digit per tile, and a scan of those counts.  Later passes see
@@ -244,12 +250,21 @@ k_scan_compact(const uint32_t *__restrict__ counts, const uint32_t *__restrict__
 // its keys and then its values pass through one array, so that a block needs about 40 KB
 // of LDS and, at 80 VGPRs, three blocks share a CU (two when both were staged at once:
 // the last of the tiles then ran as a second, mostly empty round of blocks).
-// The key count may be read from device memory; only its ceil(n / 8192) tiles are used.
+// The key count may be read from device memory; only its ceil(n / tile) tiles are used.
+//
+// Small sorts are bound by the latency of one tile, not by bandwidth: loads, 16 ranking steps one
+// after another, look-back.  They take 4 or 8 steps instead (kSmallSort, by the capacity, which
+// the host knows), and the digit totals come from atomics of one histogram kernel, with no
+// launch to scan them; their first pass looks back like the others.
 
 constexpr int kSortBlock = 512;
 constexpr int kSortWaves = kSortBlock / kWave;
-constexpr int kSortSteps = 16;
-constexpr int kSortTile = kSortBlock * kSortSteps;  // 8192 keys (fewer tiles to look back over)
+constexpr int kSortSteps = 16;  // large sorts
+// Largest capacities that take 4 and 8 steps.  Microseconds per pass with 4 / 8 / 16 steps: 2k
+// keys 4.8 / 5.7 / 8.5; 150k 8.8 / 9.3 / 13.0; 300k 9.8 / 10.4 / 13.5; 500k 11.9 / 12.0 / 14.6;
+// 760k pairs 13.2 / 13.0 / 17.6; 1.4M pairs 22.4 / 20.3 / 21.2 (more tiles to look back over).
+constexpr int64_t kSmallSort[2] = {1 << 19, 1 << 21};
+constexpr int steps_for(int64_t n_max) { return n_max <= kSmallSort[0] ? 4 : n_max <= kSmallSort[1] ? 8 : kSortSteps; }
 constexpr int kSortMaxPasses = 8;
 // Published word per (tile, digit): flag in bits 31:30, count in bits 29:0.
 constexpr uint32_t kStatAgg = 1u << 30;  // the tile's own count
@@ -258,6 +273,7 @@ constexpr uint32_t kStatCount = (1u << 30) - 1u;
 constexpr uint32_t kSortSpinLimit = 1u << 20;
 constexpr int kLookback = 8;  // earlier tiles read per look-back step (16 and 32 measured slower)
 constexpr int kHistBlocks = 1024;
+constexpr int kSmallHistBlocks = 256;  // their atomics meet on the digit totals
 
 __device__ inline int64_t sort_count(const uint32_t *n_dev, int64_t n_max) {
     if (!n_dev) return n_max;
@@ -266,7 +282,7 @@ __device__ inline int64_t sort_count(const uint32_t *n_dev, int64_t n_max) {
 }
 
 // Tiles holding the n live keys.
-__device__ inline int64_t sort_active_tiles(int64_t n) { return (n + kSortTile - 1) / kSortTile; }
+__device__ inline int64_t sort_active_tiles(int64_t n, int tile) { return (n + tile - 1) / tile; }
 
 // Per-block digit counts of the later passes (bhist) and the first pass's per-tile digit
 // counts (tcount[d * tstride + tile]): a block takes whole tiles, so the first pass finds
@@ -278,7 +294,7 @@ __global__ void __launch_bounds__(kSortBlock)
 k_radix_hist(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ n_dev, int64_t n_max, int passes,
              uint32_t *__restrict__ bhist, uint32_t *__restrict__ tcount, int64_t tstride) {
     constexpr int R = 1 << DB;
-    constexpr int kCopies = 4;
+    constexpr int kCopies = 4, kSortTile = kSortBlock * kSortSteps;
     __shared__ uint32_t h[kSortMaxPasses * R * kCopies];
     __shared__ uint32_t tc[kSortWaves][R];  // this tile's first-pass digits, one row per wave
     const int wid = threadIdx.x / kWave, lane = lane_id();
@@ -288,7 +304,7 @@ k_radix_hist(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ n_d
     // counter and the LDS atomics would serialise.
     for (int i = threadIdx.x; i < passes * R * kCopies; i += kSortBlock) h[i] = 0u;
     const int64_t n = sort_count(n_dev, n_max);
-    const int64_t tiles = sort_active_tiles(n);
+    const int64_t tiles = sort_active_tiles(n, kSortTile);
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         for (int d = lane; d < R; d += kWave) tc[wid][d] = 0u;
         __syncthreads();
@@ -324,6 +340,46 @@ k_radix_hist(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ n_d
     }
 }
 
+// Small sorts: every pass's digit totals at once, added to ghist (cleared before), and the first
+// pass's published words cleared (n_status: those of the tiles in use).
+template <int DB>
+__global__ void __launch_bounds__(kSortBlock)
+k_radix_hist_small(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ n_dev, int64_t n_max, int passes,
+                   uint32_t *__restrict__ ghist, uint32_t *__restrict__ status, int tile) {
+    constexpr int R = 1 << DB;
+    constexpr int kCopies = 4;  // as in k_radix_hist
+    __shared__ uint32_t h[kSortMaxPasses * R * kCopies];
+    const int lane = lane_id();
+    const int64_t n = sort_count(n_dev, n_max);
+    const int64_t first = (int64_t)blockIdx.x * kSortBlock + threadIdx.x, step = (int64_t)gridDim.x * kSortBlock;
+    const int64_t n_status = sort_active_tiles(n, tile) * R;
+    for (int64_t i = first; i < n_status; i += step) status[i] = 0u;
+    if ((int64_t)blockIdx.x * kSortBlock >= n) return;  // block-uniform: no keys here
+    for (int i = threadIdx.x; i < passes * R * kCopies; i += kSortBlock) h[i] = 0u;
+    __syncthreads();
+    for (int64_t base = (int64_t)blockIdx.x * kSortBlock; base < n; base += 4 * step) {
+        uint32_t k[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t i = base + q * step + threadIdx.x;
+            k[q] = i < n ? keys[i] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (base + q * step + threadIdx.x >= n) continue;
+            for (int p = 0; p < passes; ++p)
+                atomicAdd(&h[(p * R + ((k[q] >> (p * DB)) & (R - 1))) * kCopies + (lane & (kCopies - 1))], 1u);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < passes * R; i += kSortBlock) {
+        uint32_t t = 0u;
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) t += h[i * kCopies + c];
+        if (t != 0u) atomicAdd(&ghist[i], t);
+    }
+}
+
 // Exclusive prefix over the tiles of each first-pass digit's per-tile counts, in place:
 // block d scans row d and writes the digit's total to ghist[d]; it also sums digit d of
 // every later pass over the histogram blocks' partial counts into ghist[p R + d].
@@ -351,7 +407,7 @@ k_radix_tile_prefix(uint32_t *__restrict__ tcount, int64_t tstride, const uint32
         block_exclusive_scan(c[p], lds, tot);
         if (threadIdx.x == 0) ghist[p * R + d] = tot;
     }
-    const int64_t tiles = sort_active_tiles(sort_count(n_dev, n_max));
+    const int64_t tiles = sort_active_tiles(sort_count(n_dev, n_max), kSortBlock * kSortSteps);
     uint32_t *row = tcount + blockIdx.x * tstride;
     uint32_t running = 0u;
     for (int64_t base = 0; base < tiles; base += kScanTile) {
@@ -382,14 +438,14 @@ __device__ inline void store_status(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int DB>
+template <int DB, int STEPS>
 __global__ void __launch_bounds__(kSortBlock) __attribute__((amdgpu_waves_per_eu(6)))  // 3 blocks per CU
 k_radix_pass(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin, uint32_t *__restrict__ kout,
              uint32_t *__restrict__ vout, const uint32_t *__restrict__ n_dev, int64_t n_max, int shift,
              const uint32_t *__restrict__ ghist, uint32_t *__restrict__ status,
              uint32_t *__restrict__ status_next, uint32_t *__restrict__ stall, uint2 *__restrict__ ranges,
              const uint32_t *__restrict__ tprefix, int64_t tstride) {
-    constexpr int R = 1 << DB;
+    constexpr int R = 1 << DB, kSortTile = kSortBlock * STEPS;
     __shared__ uint32_t wcnt[kSortWaves][R];
     __shared__ uint32_t dstart[R];
     __shared__ uint32_t dcount[R];
@@ -400,7 +456,7 @@ k_radix_pass(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int64_t n = sort_count(n_dev, n_max);
     const int64_t tile = blockIdx.x;
-    if (tile >= sort_active_tiles(n)) return;  // block-uniform
+    if (tile >= sort_active_tiles(n, kSortTile)) return;  // block-uniform
     const uint32_t gcount = threadIdx.x < R ? ghist[threadIdx.x] : 0u;
     // With tprefix: the digit's count in all earlier tiles, loaded now so that its latency
     // passes while the tile is ranked.
@@ -409,15 +465,15 @@ k_radix_pass(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     __builtin_amdgcn_wave_barrier();
     const int64_t tile_begin = tile * kSortTile;
     const int64_t b = tile_begin + (int64_t)wid * (kSortTile / kSortWaves);
-    uint32_t key[kSortSteps], val[kSortSteps], rank[kSortSteps];
+    uint32_t key[STEPS], val[STEPS], rank[STEPS];
     // All key loads first, so that the tile is in flight at once rather than one step at a time.
 #pragma unroll
-    for (int st = 0; st < kSortSteps; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         const int64_t i = b + st * kWave + lane;
         key[st] = i < n ? kin[i] : 0u;
     }
 #pragma unroll
-    for (int st = 0; st < kSortSteps; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         const bool act = b + st * kWave + lane < n;
         const uint32_t d = (key[st] >> shift) & (R - 1);
         const uint64_t a = ballot(act);
@@ -469,14 +525,14 @@ k_radix_pass(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     // the values are loaded: fewer registers are live through the look-back, and the loads'
     // latency passes during it. rank[] becomes the position in the sorted tile.
 #pragma unroll
-    for (int st = 0; st < kSortSteps; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         if (rank[st] == 0xffffffffu) continue;
         const uint32_t d = (key[st] >> shift) & (R - 1);
         rank[st] += dstart[d] + wcnt[wid][d];
         lk[rank[st]] = key[st];
     }
 #pragma unroll
-    for (int st = 0; st < kSortSteps; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         const int64_t i = b + st * kWave + lane;
         val[st] = i < n ? vin[i] : 0u;
     }
@@ -528,7 +584,7 @@ k_radix_pass(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     // so that three blocks fit on a CU.
     const int cnt = (int)(n - tile_begin < kSortTile ? n - tile_begin : kSortTile);
 #pragma unroll
-    for (int st = 0; st < kSortSteps; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         const int j = threadIdx.x + st * kSortBlock;
         if (j >= cnt) continue;
         const uint32_t k = lk[j];
@@ -549,11 +605,11 @@ k_radix_pass(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     }
     __syncthreads();
 #pragma unroll
-    for (int st = 0; st < kSortSteps; ++st)
+    for (int st = 0; st < STEPS; ++st)
         if (rank[st] != 0xffffffffu) lk[rank[st]] = val[st];
     __syncthreads();
 #pragma unroll
-    for (int st = 0; st < kSortSteps; ++st) {
+    for (int st = 0; st < STEPS; ++st) {
         const int j = threadIdx.x + st * kSortBlock;
         if (j >= cnt) continue;
         const uint32_t k = key[st];
@@ -598,7 +654,7 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
          uint32_t *__restrict__ pval, FrameHeader *__restrict__ hdr, uint32_t cap,
          const uint32_t *__restrict__ total, uint32_t *__restrict__ big_list, uint32_t *__restrict__ big_count,
          const uint32_t *__restrict__ n_dev, uint2 *__restrict__ ranges, uint32_t *__restrict__ twork,
-         int64_t n_tiles) {
+         int64_t n_tiles, uint32_t *__restrict__ clear, int n_clear) {
     __shared__ uint32_t row_pos[kKeygenWaves][kKeygenRows];   // first output position
     __shared__ uint32_t row_tile[kKeygenWaves][kKeygenRows];  // global tile id of the first tile
     __shared__ uint32_t row_rec[kKeygenWaves][kKeygenRows];   // record index
@@ -612,6 +668,8 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
         ranges[t] = make_uint2(0xffffffffu, 0u);
         twork[t] = 0u;
     }
+    // The tile sort's digit totals, likewise.
+    for (int64_t t = p; t < n_clear; t += (int64_t)gridDim.x * blockDim.x) clear[t] = 0u;
     if (p == 0) {
         // Everything a backward checks before it reads the frame state.
         const uint32_t t = *total;
@@ -799,7 +857,7 @@ hipError_t launch_scan_indirect(const uint32_t *counts, const uint32_t *idx, int
     // apply pass reads it back contiguously instead of gathering a second time.
     if (!idx) gathered = nullptr;
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanBlock), 0, s, counts, idx, n_dev, n, flag, part,
-                       gathered);
+                       gathered, nullptr, 0);
     if (gathered)
         hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(kScanBlock), 0, s, gathered, nullptr, n_dev, n, 0,
                            part, offsets, total, clear);
@@ -810,29 +868,41 @@ hipError_t launch_scan_indirect(const uint32_t *counts, const uint32_t *idx, int
 }
 
 hipError_t launch_compact(const uint32_t *counts, const uint32_t *dkey, int64_t n, uint32_t *ckey, uint32_t *cval,
-                          uint32_t *n_live, uint32_t *part, bool pack, hipStream_t s) {
+                          uint32_t *n_live, uint32_t *part, bool pack, uint32_t *clear, int n_clear, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     if (pack && n > (int64_t)kPackMask + 1) return hipErrorInvalidValue;
     const int64_t nb = scan_blocks(n);
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanBlock), 0, s, counts, nullptr, nullptr, n, 1, part,
-                       nullptr);
+                       nullptr, clear, n_clear);
     hipLaunchKernelGGL(k_scan_compact, dim3((unsigned)nb), dim3(kScanBlock), 0, s, counts, dkey, n, part, ckey, cval,
                        pack ? 1 : 0, n_live);
     return hipGetLastError();
 }
 
-static int64_t sort_tiles(int64_t n_max) { return (n_max + kSortTile - 1) / kSortTile; }
-
-// Scratch words: digit histograms [kSortMaxPasses << digit_bits], published words
-// [2][tiles << digit_bits] (alternating passes), the first pass's per-tile digit offsets
-// [tiles << digit_bits] and the histogram blocks' partial counts.
-int64_t radix_hist_words(int64_t n_max, int digit_bits) {
-    const int64_t t = sort_tiles(n_max) > 0 ? sort_tiles(n_max) : 1;
-    const int64_t hb = t < kHistBlocks ? t : kHistBlocks;
-    return ((int64_t)kSortMaxPasses << digit_bits) * (1 + hb) + 3 * (t << digit_bits);
+static int64_t sort_tiles(int64_t n_max) {
+    const int64_t tile = (int64_t)kSortBlock * steps_for(n_max);
+    return n_max > 0 ? (n_max + tile - 1) / tile : 1;
 }
 
-template <int DB>
+// Scratch words: digit histograms [kSortMaxPasses << digit_bits], published words
+// [2][tiles << digit_bits] (alternating passes), and for large sorts the first pass's per-tile digit
+// offsets [tiles << digit_bits] and the histogram blocks' partial counts.  Not less for
+// more keys, although those may take fewer tiles.
+int64_t radix_hist_words(int64_t n_max, int digit_bits) {
+    auto words = [&](int64_t n) {
+        const int64_t t = sort_tiles(n), hist = (int64_t)kSortMaxPasses << digit_bits;
+        if (steps_for(n) < kSortSteps) return hist + 2 * (t << digit_bits);
+        return hist * (1 + (t < kHistBlocks ? t : kHistBlocks)) + 3 * (t << digit_bits);
+    };
+    int64_t w = words(n_max);
+    for (int64_t small : kSmallSort)
+        if (small < n_max) w = std::max(w, words(small));
+    return w;
+}
+
+int radix_total_words(int digit_bits) { return kSortMaxPasses << digit_bits; }
+
+template <int DB, int STEPS>
 static void sort_passes(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_tmp, uint32_t *vals_tmp,
                         uint32_t *keys_out, uint32_t *vals_out, int64_t n_max, const uint32_t *n_dev, int passes,
                         uint32_t *scratch, uint32_t *stall, uint2 *ranges, bool keep_keys, hipStream_t s) {
@@ -840,21 +910,27 @@ static void sort_passes(const uint32_t *keys_in, const uint32_t *vals_in, uint32
     const int64_t tiles = sort_tiles(n_max);
     uint32_t *ghist = scratch;
     uint32_t *status[2] = {ghist + (int64_t)kSortMaxPasses * R, ghist + (int64_t)kSortMaxPasses * R + tiles * R};
-    uint32_t *tprefix = status[1] + tiles * R;  // [R][tiles]: the first pass's per-tile digit offsets
-    uint32_t *bhist = tprefix + tiles * R;      // [hist blocks][passes][R]
-    int64_t hb = tiles < kHistBlocks ? tiles : kHistBlocks;
-    if (hb < 1) hb = 1;
-    hipLaunchKernelGGL(k_radix_hist<DB>, dim3((unsigned)hb), dim3(kSortBlock), 0, s, keys_in, n_dev, n_max, passes,
-                       bhist, tprefix, tiles);
-    hipLaunchKernelGGL(k_radix_tile_prefix<DB>, dim3(R), dim3(kScanBlock), 0, s, tprefix, tiles, n_dev, n_max, passes,
-                       bhist, (int)hb, ghist);
+    uint32_t *tprefix = nullptr;  // [R][tiles]: the first pass's per-tile digit offsets
+    if (STEPS < kSortSteps) {
+        const int64_t hb = std::min<int64_t>((n_max + 4 * kSortBlock - 1) / (4 * kSortBlock), kSmallHistBlocks);
+        hipLaunchKernelGGL(k_radix_hist_small<DB>, dim3((unsigned)hb), dim3(kSortBlock), 0, s, keys_in, n_dev, n_max,
+                           passes, ghist, status[0], kSortBlock * STEPS);
+    } else {
+        tprefix = status[1] + tiles * R;
+        uint32_t *bhist = tprefix + tiles * R;  // [hist blocks][passes][R]
+        const int64_t hb = std::min<int64_t>(tiles, kHistBlocks);
+        hipLaunchKernelGGL(k_radix_hist<DB>, dim3((unsigned)hb), dim3(kSortBlock), 0, s, keys_in, n_dev, n_max, passes,
+                           bhist, tprefix, tiles);
+        hipLaunchKernelGGL(k_radix_tile_prefix<DB>, dim3(R), dim3(kScanBlock), 0, s, tprefix, tiles, n_dev, n_max,
+                           passes, bhist, (int)hb, ghist);
+    }
     const uint32_t *kin = keys_in, *vin = vals_in;
     for (int p = 0; p < passes; ++p) {
         // The last pass writes to *_out; earlier passes alternate so that this holds.
         const bool to_out = ((passes - 1 - p) % 2) == 0;
         uint32_t *ko = to_out ? keys_out : keys_tmp;
         uint32_t *vo = to_out ? vals_out : vals_tmp;
-        hipLaunchKernelGGL(k_radix_pass<DB>, dim3((unsigned)tiles), dim3(kSortBlock), 0, s, kin, vin,
+        hipLaunchKernelGGL((k_radix_pass<DB, STEPS>), dim3((unsigned)tiles), dim3(kSortBlock), 0, s, kin, vin,
                            p == passes - 1 && !keep_keys ? nullptr : ko, vo, n_dev,
                            n_max, p * DB, ghist + (int64_t)p * R, status[p & 1], status[(p + 1) & 1], stall,
                            p == passes - 1 ? ranges : nullptr, p == 0 ? tprefix : nullptr, tiles);
@@ -876,13 +952,25 @@ hipError_t radix_sort(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t
     if (passes > kSortMaxPasses) return hipErrorInvalidValue;
     int db = (bits + passes - 1) / passes;
     if (db < 4) db = 4;
+#define GSPM_SORT(DB, STEPS)                                                                                     \
+    sort_passes<DB, STEPS>(keys_in, vals_in, keys_tmp, vals_tmp, keys_out, vals_out, n_max, n_dev, passes, scratch, \
+                           stall, ranges, keep_keys, s)
+#define GSPM_SORT_DB(DB)                          \
+    do {                                          \
+        if (steps == 4) GSPM_SORT(DB, 4);         \
+        else if (steps == 8) GSPM_SORT(DB, 8);    \
+        else GSPM_SORT(DB, kSortSteps);           \
+    } while (0)
+    const int steps = steps_for(n_max);
     switch (db) {
-        case 4: sort_passes<4>(keys_in, vals_in, keys_tmp, vals_tmp, keys_out, vals_out, n_max, n_dev, passes, scratch, stall, ranges, keep_keys, s); break;
-        case 5: sort_passes<5>(keys_in, vals_in, keys_tmp, vals_tmp, keys_out, vals_out, n_max, n_dev, passes, scratch, stall, ranges, keep_keys, s); break;
-        case 6: sort_passes<6>(keys_in, vals_in, keys_tmp, vals_tmp, keys_out, vals_out, n_max, n_dev, passes, scratch, stall, ranges, keep_keys, s); break;
-        case 7: sort_passes<7>(keys_in, vals_in, keys_tmp, vals_tmp, keys_out, vals_out, n_max, n_dev, passes, scratch, stall, ranges, keep_keys, s); break;
-        default: sort_passes<8>(keys_in, vals_in, keys_tmp, vals_tmp, keys_out, vals_out, n_max, n_dev, passes, scratch, stall, ranges, keep_keys, s); break;
+        case 4: GSPM_SORT_DB(4); break;
+        case 5: GSPM_SORT_DB(5); break;
+        case 6: GSPM_SORT_DB(6); break;
+        case 7: GSPM_SORT_DB(7); break;
+        default: GSPM_SORT_DB(8); break;
     }
+#undef GSPM_SORT_DB
+#undef GSPM_SORT
     return hipGetLastError();
 }
 
@@ -891,12 +979,12 @@ hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const ui
                          int64_t n_records, int64_t n_per_view,
                          const ViewTable &vt, uint32_t *pkey, uint32_t *pval, FrameHeader *hdr, uint32_t capacity,
                          const uint32_t *total, uint32_t *big_list, uint32_t *big_count, const uint32_t *n_dev,
-                         uint2 *ranges, uint32_t *twork, int64_t n_tiles, hipStream_t s) {
+                         uint2 *ranges, uint32_t *twork, int64_t n_tiles, uint32_t *clear, int n_clear, hipStream_t s) {
     const float4 *rec = reinterpret_cast<const float4 *>(records);
     const int64_t nb = n_records > 0 ? (n_records + 255) / 256 : 1;
     hipLaunchKernelGGL(k_keygen, dim3((unsigned)nb), dim3(256), 0, s, sorted_rec, rec_mask, sorted_counts, offsets, rec,
                        spans, rs, n_records, n_per_view, vt, pkey, pval, hdr, capacity, total, big_list, big_count,
-                       n_dev, ranges, twork, n_tiles);
+                       n_dev, ranges, twork, n_tiles, clear, n_clear);
     if (n_records > 0)
         hipLaunchKernelGGL(k_keygen_big, dim3(1024), dim3(256), 0, s, sorted_rec, rec_mask, offsets, rec, rs,
                            n_per_view, vt, pkey, pval, capacity, big_list, big_count);

@@ -434,18 +434,20 @@ hipError_t launch_scan_indirect(const uint32_t *counts, const uint32_t *idx, int
 // and writes their number to *n_live; with pack, the value also carries the pair count
 // (see kPackShift).  part: scratch of at least scan_partials(n) words.
 hipError_t launch_compact(const uint32_t *counts, const uint32_t *dkey, int64_t n, uint32_t *ckey, uint32_t *cval,
-                          uint32_t *n_live, uint32_t *part, bool pack, hipStream_t s);
+                          uint32_t *n_live, uint32_t *part, bool pack, uint32_t *clear, int n_clear, hipStream_t s);
 
 // Stable LSD radix sort of (key, value) uint32 pairs over the low `bits` key bits, in
 // ceil(bits / digit_bits) passes of equal width (digit_bits in [4, 8]).  n_dev: device
 // count (may be NULL: n_max is then exact).  Buffers: keys/vals in, tmp, out (the sorted
-// result ends in keys_out/vals_out).  scratch: radix_hist_words(n_max, digit_bits) words.
+// result ends in keys_out/vals_out).  scratch: radix_hist_words(n_max, digit_bits) words, of which
+// the caller clears the first radix_total_words(digit_bits) (launch_compact and launch_keygen do).
 // *stall (device) is set if a pass gave up waiting for an earlier tile (the result is
 // then invalid); the caller clears it.  ranges (optional): the keys are tile ids and the
 // final pass writes each tile's [first, end) positions; the caller fills it with
 // (0xffffffff, 0) beforehand, which empty tiles keep.  keep_keys = false: the final pass
 // writes only the values (keys_out then holds an earlier pass's keys).
 int64_t radix_hist_words(int64_t n_max, int digit_bits);
+int radix_total_words(int digit_bits);
 hipError_t radix_sort(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_tmp,
                       uint32_t *vals_tmp, uint32_t *keys_out, uint32_t *vals_out, int64_t n_max,
                       const uint32_t *n_dev, int bits, int digit_bits, uint32_t *scratch, uint32_t *stall,
@@ -462,7 +464,8 @@ hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const ui
                          int64_t n_records, int64_t n_per_view,
                          const ViewTable &vt, uint32_t *pkey, uint32_t *pval, FrameHeader *hdr,
                          uint32_t capacity, const uint32_t *total, uint32_t *big_list, uint32_t *big_count,
-                         const uint32_t *n_dev, uint2 *ranges, uint32_t *twork, int64_t n_tiles, hipStream_t s);
+                         const uint32_t *n_dev, uint2 *ranges, uint32_t *twork, int64_t n_tiles, uint32_t *clear,
+                         int n_clear, hipStream_t s);
 
 hipError_t launch_sum_u64(const uint32_t *x, int64_t n, unsigned long long *out, hipStream_t s);
 
