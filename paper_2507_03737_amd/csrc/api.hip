@@ -206,7 +206,8 @@ hipError_t ensure_records(gspm_ctx *c, int64_t R, int digit_bits) {
     const int64_t w = R > 0 ? R : 1;
     hipError_t e;
     if ((e = grow(c->counts, 4 * w))) return e;
-    if ((e = grow(c->big, 4 * w))) return e;
+    // Live and large bits of every 64 records of a view, then the large bits in depth order.
+    if ((e = grow(c->big, 8 * (3 * (w / kWave) + 2 * kMaxViews + 1)))) return e;
     if ((e = grow(c->live, 4 * w))) return e;
     if ((e = grow(c->dkey, 4 * w))) return e;
     if ((e = grow(c->dval, 4 * w))) return e;
@@ -384,21 +385,24 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
 
     // 1. Project every (Gaussian, view) record.
     PhaseTimer t_pre(ctx, hs, GSPM_PHASE_PREPROCESS);
+    const int64_t n_per_view = g->n > 0 ? g->n : 1;
+    uint64_t *live = static_cast<uint64_t *>(ctx->big.p);
+    uint64_t *large = live + 2 * P.vt.n_views * live_waves(n_per_view);  // of the records in depth order
     GSPM_HIP(launch_preprocess(*g, P.vt, views->T_cw, P.rs, records, counts, static_cast<uint32_t *>(ctx->dkey.p),
-                               static_cast<uint4 *>(ctx->spans.p), static_cast<uint32_t *>(ctx->big.p), total + 1,
-                               &hdr->sort_stall, hs));
+                               static_cast<uint4 *>(ctx->spans.p), live, &hdr->sort_stall, hist, radix_total_words(db),
+                               hs));
     t_pre.stop();
-    // Device-side counts: total[0] tile pairs, total[1] queued large records, total[2] live records.
-    uint32_t *n_live = total + 2;
+    // Device-side counts: total[0] tile pairs, total[1] live records.
+    uint32_t *n_live = total + 1;
     // Small enough windows carry each live record's pair count through the depth sort.
     const bool pack = R <= (int64_t)kPackMask + 1;
     if (R > 0) {
         // 2. Keep the records that have tile pairs (in record order) and sort them by float32
         //    depth (stable, so ties keep record order).
         PhaseTimer t_ds(ctx, hs, GSPM_PHASE_DEPTH_SORT);
-        GSPM_HIP(launch_compact(counts, static_cast<uint32_t *>(ctx->dkey.p), R, static_cast<uint32_t *>(ctx->dval.p),
-                                static_cast<uint32_t *>(ctx->live.p), n_live, part, pack, hist, radix_total_words(db),
-                                hs));
+        GSPM_HIP(launch_compact(counts, static_cast<uint32_t *>(ctx->dkey.p), live, records, P.vt, P.rs, n_per_view,
+                                static_cast<uint32_t *>(ctx->dval.p), static_cast<uint32_t *>(ctx->live.p), n_live,
+                                part, pack, hs));
         GSPM_HIP(radix_sort(static_cast<uint32_t *>(ctx->dval.p), static_cast<uint32_t *>(ctx->live.p),
                             static_cast<uint32_t *>(ctx->dkey_tmp.p), static_cast<uint32_t *>(ctx->dval_tmp.p),
                             static_cast<uint32_t *>(ctx->dkey_s.p), static_cast<uint32_t *>(ctx->dval_s.p), R, n_live,
@@ -411,23 +415,30 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
         // The sorted depth keys are no longer needed: their buffer receives the pair counts
         // in depth order, unpacked (or gathered) once by the scan.
         GSPM_HIP(launch_scan_indirect(counts, static_cast<uint32_t *>(ctx->dval_s.p), R,
-                                      static_cast<uint32_t *>(ctx->offsets.p), total, part, hs, n_live, pack ? 2 : 0,
-                                      static_cast<uint32_t *>(ctx->dkey_s.p), total + 1));  // + the emitter's queue count
+                                      static_cast<uint32_t *>(ctx->offsets.p), total, part, hs, n_live, pack,
+                                      static_cast<uint32_t *>(ctx->dkey_s.p)));
     } else {
-        GSPM_HIP(launch_fill_u32(total, 0u, 3, hs));
+        GSPM_HIP(launch_fill_u32(total, 0u, 2, hs));
     }
     // 4. Emit (tile, record) pairs; the header gets the pair count and overflow flag.  The
-    //    emitter also clears the per-tile work that the forward's waves raise.
+    //    emitter also clears what later kernels raise.
     GSPM_HIP(grow(ctx->twork, 4 * (P.n_tiles > 0 ? P.n_tiles : 1)));
     uint32_t *twork = static_cast<uint32_t *>(ctx->twork.p);
+    uint8_t *visible = P.rs.mark_visible ? at<uint8_t>(frame_state, L0.visible) : nullptr;
+    KeygenClears clr = {};
+    clr.twork = twork;
+    clr.n_tiles = P.n_tiles;
+    clr.digits = hist;
+    clr.n_digits = radix_total_words(db);
+    clr.visible = reinterpret_cast<uint32_t *>(visible);
+    clr.n_visible = visible ? (R + 3) / 4 : 0;
+    clr.wmask = wmask_at(pair_vals, cap);
+    clr.n_wmask = wmask_stride(cap) * (P.vt.tile * P.vt.tile / P.vt.ppt / kWave);
     GSPM_HIP(launch_keygen(static_cast<uint32_t *>(ctx->dval_s.p), pack ? kPackMask : 0xffffffffu,
-                           static_cast<uint32_t *>(ctx->dkey_s.p),
-                           static_cast<uint32_t *>(ctx->offsets.p),
-                           records, static_cast<const uint4 *>(ctx->spans.p), P.rs, R, g->n > 0 ? g->n : 1, P.vt,
-                           static_cast<uint32_t *>(ctx->pkey.p),
-                           static_cast<uint32_t *>(ctx->pval.p), hdr, (uint32_t)cap, total,
-                           static_cast<uint32_t *>(ctx->big.p), total + 1, n_live, ranges, twork, P.n_tiles, hist,
-                           radix_total_words(db), hs));
+                           static_cast<uint32_t *>(ctx->dkey_s.p), static_cast<uint32_t *>(ctx->offsets.p), records,
+                           static_cast<const uint4 *>(ctx->spans.p), P.rs, R, n_per_view, P.vt,
+                           static_cast<uint32_t *>(ctx->pkey.p), static_cast<uint32_t *>(ctx->pval.p), hdr,
+                           (uint32_t)cap, total, large, n_live, ranges, clr, hs));
     t_bin.stop();
     // 5. Stable sort by tile id; its final pass writes the per-tile ranges (6).
     if (cap > 0) {
@@ -443,20 +454,11 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
     uint32_t *order = at<uint32_t>(frame_state, L0.order);
     GSPM_HIP(launch_order_tiles(ranges, nullptr, P.n_tiles, order, hs));
     // 7. Composite (optionally marking the records that contribute to a pixel).
-    uint8_t *visible = nullptr;
-    if (P.rs.mark_visible) {
-        visible = at<uint8_t>(frame_state, L0.visible);
-        GSPM_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(visible), 0u, (R + 3) / 4, hs));
-    }
-    uint64_t *wmask = wmask_at(pair_vals, cap);
-    const int64_t wstride = wmask_stride(cap);
-    GSPM_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(wmask), 0u,
-                             2 * wstride * (P.vt.tile * P.vt.tile / P.vt.ppt / kWave), hs));
     PhaseTimer t_fwd(ctx, hs, GSPM_PHASE_RASTER_FWD);
     GSPM_HIP(launch_raster_forward(P.vt, P.rs, ranges, pair_vals, records, out->rgb, out->depth, out->alpha,
                                    out->pointmap, at<float>(frame_state, L0.t_final), at<uint32_t>(frame_state, L0.last),
-                                   at<uint32_t>(frame_state, L0.contrib), visible, order, twork, wmask, wstride, hdr,
-                                   hs));
+                                   at<uint32_t>(frame_state, L0.contrib), visible, order, twork, clr.wmask, wmask_stride(cap),
+                                   hdr, hs));
     GSPM_HIP(launch_order_tiles(nullptr, twork, P.n_tiles, order + P.n_tiles, hs));
     return GSPM_OK;
 }

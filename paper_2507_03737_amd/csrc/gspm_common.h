@@ -405,12 +405,17 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t value, int64_t n, hipStream_t s
 hipError_t launch_fill_f32(float *p, float value, int64_t n, hipStream_t s);
 
 // Projects every record and counts its tile pairs, caching the tile-row spans of records
-// with pairs in spans [N V]; big_list / big_count are scratch for the records counted by
-// whole waves (big_count is zeroed here, and clear_also, if not NULL, in the same launch).
+// with pairs in spans [N V].  Per view and 64 consecutive Gaussians (a segment), a word of live
+// says which have pairs (counts and dkey hold nothing for the others), and after all these
+// words as many say which of them are large: these have counts = kBigCount until
+// launch_compact has counted them.  clear_one (may be NULL) and clear[n_clear] are zeroed in
+// the same launch.
+constexpr uint32_t kBigCount = 1u << 31;  // a large record's count: this bit, and the count below it
+__host__ __device__ inline int64_t live_waves(int64_t n) { return (n + kWave - 1) / kWave; }
 hipError_t launch_preprocess(const gspm_gaussians &g, const ViewTable &vt, const float *T_cw,
                              const RasterSettings &rs, float *records, uint32_t *counts,
-                             uint32_t *dkey, uint4 *spans, uint32_t *big_list, uint32_t *big_count,
-                             uint32_t *clear_also, hipStream_t s);
+                             uint32_t *dkey, uint4 *spans, uint64_t *live, uint32_t *clear_one, uint32_t *clear,
+                             int n_clear, hipStream_t s);
 
 // A window of at most 2^kPackShift records carries each live record through the depth sort
 // as its index with its pair count in the top bits, so that the pair-offset scan reads
@@ -420,27 +425,25 @@ constexpr uint32_t kPackShift = 26;
 constexpr uint32_t kPackMask = (1u << kPackShift) - 1u;
 constexpr uint32_t kPackCountMax = (1u << (32 - kPackShift)) - 1u;
 
-// Exclusive scan for p < n of: counts[idx[p]] (flag 0), counts[idx[p]] != 0 (flag 1), or
-// the pair count packed in idx[p] (flag 2); idx NULL means the identity.  n is
-// min(*n_dev, n) when n_dev is given.  Writes offsets[p] and the total to *total.  part:
-// scratch of at least scan_partials(n) words.
-int64_t scan_partials(int64_t n);
+// Exclusive scan for p < min(*n_dev, n) of counts[idx[p]] or, with packed, of the pair count
+// packed in idx[p] (see kPackShift), which also go to gathered[p].  Writes offsets[p] and the
+// total to *total.  part: kScanMaxBlocks words of scratch.
 hipError_t launch_scan_indirect(const uint32_t *counts, const uint32_t *idx, int64_t n,
                                 uint32_t *offsets, uint32_t *total, uint32_t *part, hipStream_t s,
-                                const uint32_t *n_dev = nullptr, int flag = 0, uint32_t *gathered = nullptr,
-                                uint32_t *clear = nullptr);
+                                const uint32_t *n_dev, bool packed, uint32_t *gathered);
 
-// Compacts (depth key, record index) of the records with counts[r] != 0, in record order,
-// and writes their number to *n_live; with pack, the value also carries the pair count
-// (see kPackShift).  part: scratch of at least scan_partials(n) words.
-hipError_t launch_compact(const uint32_t *counts, const uint32_t *dkey, int64_t n, uint32_t *ckey, uint32_t *cval,
-                          uint32_t *n_live, uint32_t *part, bool pack, uint32_t *clear, int n_clear, hipStream_t s);
+// Compacts (depth key, record index) of the records that live marks, in record order, and
+// writes their number to *n_live; with pack, the value also carries the pair count (see
+// kPackShift).  Counts the pairs of the large records.  part: kScanMaxBlocks words of scratch.
+hipError_t launch_compact(uint32_t *counts, const uint32_t *dkey, const uint64_t *live, const float *records,
+                          const ViewTable &vt, const RasterSettings &rs, int64_t n_per_view, uint32_t *ckey,
+                          uint32_t *cval, uint32_t *n_live, uint32_t *part, bool pack, hipStream_t s);
 
 // Stable LSD radix sort of (key, value) uint32 pairs over the low `bits` key bits, in
 // ceil(bits / digit_bits) passes of equal width (digit_bits in [4, 8]).  n_dev: device
 // count (may be NULL: n_max is then exact).  Buffers: keys/vals in, tmp, out (the sorted
 // result ends in keys_out/vals_out).  scratch: radix_hist_words(n_max, digit_bits) words, of which
-// the caller clears the first radix_total_words(digit_bits) (launch_compact and launch_keygen do).
+// the caller clears the first radix_total_words(digit_bits) (launch_preprocess and launch_keygen do).
 // *stall (device) is set if a pass gave up waiting for an earlier tile (the result is
 // then invalid); the caller clears it.  ranges (optional): the keys are tile ids and the
 // final pass writes each tile's [first, end) positions; the caller fills it with
@@ -453,19 +456,32 @@ hipError_t radix_sort(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t
                       const uint32_t *n_dev, int bits, int digit_bits, uint32_t *scratch, uint32_t *stall,
                       uint2 *ranges, hipStream_t s, bool keep_keys = true);
 
-// Emits the (global tile, record) pairs of every record in depth order.  Records with
-// more than kBigRecord pairs are queued in big_list (big_count must be zero on entry: the
-// pair-offset scan clears it) and emitted by whole waves.  records: the projected records (for the support footprint of records
-// whose spans are not cached in spans).  It also fills ranges [n_tiles] with the empty
-// range (0xffffffff, 0) that the tile sort's last pass narrows, and twork [n_tiles] with 0.
-// rec_mask: kPackMask if sorted_rec carries packed counts, else all ones.
+// What the emission clears for later kernels, to save their launches: the tile ranges (given to it
+// as such), the per-tile work, the tile sort's digit totals, the visible marks and the
+// contribution bits.
+struct KeygenClears {
+    uint32_t *twork;
+    int64_t n_tiles;
+    uint32_t *digits;
+    int64_t n_digits;
+    uint32_t *visible;
+    int64_t n_visible;
+    uint64_t *wmask;
+    int64_t n_wmask;
+};
+
+// Emits the (global tile, record) pairs of every record in depth order.  Records with more than
+// kBigRecord pairs are marked in large (one word per 64 sorted records) and emitted by whole
+// waves.  records: the projected records (for the support footprint of records whose spans are not
+// cached in spans).  It also fills ranges [n_tiles] with the empty range (0xffffffff, 0) that the
+// tile sort's last pass narrows.  rec_mask: kPackMask if sorted_rec carries packed counts,
+// else all ones.
 hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const uint32_t *sorted_counts,
                          const uint32_t *offsets, const float *records, const uint4 *spans, const RasterSettings &rs,
                          int64_t n_records, int64_t n_per_view,
                          const ViewTable &vt, uint32_t *pkey, uint32_t *pval, FrameHeader *hdr,
-                         uint32_t capacity, const uint32_t *total, uint32_t *big_list, uint32_t *big_count,
-                         const uint32_t *n_dev, uint2 *ranges, uint32_t *twork, int64_t n_tiles, uint32_t *clear,
-                         int n_clear, hipStream_t s);
+                         uint32_t capacity, const uint32_t *total, uint64_t *large, const uint32_t *n_dev,
+                         uint2 *ranges, const KeygenClears &clr, hipStream_t s);
 
 hipError_t launch_sum_u64(const uint32_t *x, int64_t n, unsigned long long *out, hipStream_t s);
 

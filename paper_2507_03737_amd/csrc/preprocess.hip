@@ -125,20 +125,25 @@ __device__ inline void project_view(const float *T12, float fx, float fy, float 
 __global__ void __launch_bounds__(256)
 k_preprocess(gspm_gaussians G, ViewTable vt, const float *__restrict__ T_cw, RasterSettings rs,
              float4 *__restrict__ rec, uint32_t *__restrict__ counts, uint32_t *__restrict__ dkey,
-             uint4 *__restrict__ spans, uint32_t *__restrict__ big_list, uint32_t *__restrict__ big_count) {
+             uint4 *__restrict__ spans, uint64_t *__restrict__ live, uint32_t *__restrict__ clear_one,
+             uint32_t *__restrict__ clear, int n_clear) {
     // One thread per Gaussian looping over the views: the view-independent part of the
     // projection is computed once.
     const int64_t n = G.n;
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x == 0) {  // words of later kernels, cleared here to save a launch
+        if (threadIdx.x == 0 && clear_one) *clear_one = 0u;
+        for (int i = threadIdx.x; i < n_clear; i += blockDim.x) clear[i] = 0u;
+    }
     Proj P;
     const bool framed = g < n && gaussian_frame(G, g, n, P);
     for (int v = 0; v < vt.n_views; ++v) {
         const int64_t r = (int64_t)v * n + g;
         bool big = false;
+        uint32_t count = 0;
         if (g < n) {
             if (framed)
                 project_view(T_cw + 12 * v, vt.fx[v], vt.fy[v], vt.cx[v], vt.cy[v], vt.width[v], vt.height[v], rs, P);
-            uint32_t count = 0;
             if (framed && P.visible) {
                 const float zf = (float)P.z;
                 dkey[r] = __float_as_uint(zf);
@@ -169,6 +174,7 @@ k_preprocess(gspm_gaussians G, ViewTable vt, const float *__restrict__ T_cw, Ras
                     const int rows = (f.j1 >> sh) - (f.j0 >> sh) + 1, cols = (f.i1 >> sh) - (f.i0 >> sh) + 1;
                     if ((uint32_t)(rows * cols) > kBigRecord) {
                         big = true;  // its count may still come out at most kBigRecord: not cached
+                        count = kBigCount;
                         spans[r] = make_uint4(kSpanNone << 16, 0u, 0u, 0u);
                     } else {
                         uint32_t w[kSpanRows] = {1u, 1u, 1u};  // empty rows: first > last
@@ -198,36 +204,17 @@ k_preprocess(gspm_gaussians G, ViewTable vt, const float *__restrict__ T_cw, Ras
                     }
                 }
             }
-            counts[r] = count;
+            if (count != 0u) counts[r] = count;
         }
-        const uint32_t slot = wave_append(big_count, big);
-        if (big) big_list[slot] = (uint32_t)r;
-    }
-}
-
-// Exact pair count of the queued large records: one wave per record, one lane per tile row.
-__global__ void __launch_bounds__(256)
-k_count_big(const float4 *__restrict__ rec, ViewTable vt, RasterSettings rs, int64_t n_per_view,
-            uint32_t *__restrict__ counts, const uint32_t *__restrict__ big_list,
-            const uint32_t *__restrict__ big_count) {
-    const int lane = lane_id();
-    const uint32_t n_big = *big_count;
-    const uint32_t n_waves = gridDim.x * (blockDim.x / kWave);
-    for (uint32_t w = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave; w < n_big; w += n_waves) {
-        const uint32_t r = big_list[w];
-        const int v = (int)(r / (uint32_t)n_per_view);
-        Footprint f;
-        uint32_t count = 0;
-        if (record_footprint(rec[4 * (int64_t)r], rec[4 * (int64_t)r + 1], rs.alpha_min, vt.width[v],
-                             vt.height[v], f)) {
-            const int T = vt.tile, sh = __builtin_ctz((unsigned)vt.tile);
-            for (int ty = (f.j0 >> sh) + lane; ty <= f.j1 >> sh; ty += kWave) {
-                int ta, tb;
-                if (row_span(f, T, ty, ta, tb)) count += (uint32_t)(tb - ta + 1);
-            }
+        // Which of the wave's records have pairs, and which of them are large: two words, where
+        // a queue of the large ones cost an atomic on one address per wave and view (9 ns each,
+        // one after another: half of the kernel's time).
+        const uint64_t has = ballot(count != 0u), large = ballot(big);
+        if (lane_id() == 0 && g < n) {
+            const int64_t seg = v * live_waves(n) + g / kWave;
+            live[seg] = has;
+            live[vt.n_views * live_waves(n) + seg] = large;
         }
-        for (int off = 32; off > 0; off >>= 1) count += __shfl_xor(count, off, 64);
-        if (lane == 0) counts[r] = count;
     }
 }
 
@@ -457,14 +444,6 @@ k_pose_reduce(const double *__restrict__ part, int64_t nblocks, float *__restric
     }
 }
 
-// Zeroes one or two counters in one launch.
-__global__ void k_clear2(uint32_t *a, uint32_t *b) {
-    if (threadIdx.x == 0) {
-        *a = 0u;
-        if (b) *b = 0u;
-    }
-}
-
 __global__ void k_fill_u32(uint32_t *p, uint32_t value, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = value;
@@ -536,15 +515,12 @@ hipError_t launch_fill_f32(float *p, float value, int64_t n, hipStream_t s) {
 
 hipError_t launch_preprocess(const gspm_gaussians &g, const ViewTable &vt, const float *T_cw,
                              const RasterSettings &rs, float *records, uint32_t *counts,
-                             uint32_t *dkey, uint4 *spans, uint32_t *big_list, uint32_t *big_count,
-                             uint32_t *clear_also, hipStream_t s) {
+                             uint32_t *dkey, uint4 *spans, uint64_t *live, uint32_t *clear_one, uint32_t *clear,
+                             int n_clear, hipStream_t s) {
     const int64_t R = g.n * vt.n_views;
-    if (R <= 0) return clear_also ? launch_fill_u32(clear_also, 0u, 1, s) : hipSuccess;
-    hipLaunchKernelGGL(k_clear2, dim3(1), dim3(64), 0, s, big_count, clear_also);
-    hipLaunchKernelGGL(k_preprocess, dim3((unsigned)((g.n + 255) / 256), 1u), dim3(256), 0, s, g,
-                       vt, T_cw, rs, reinterpret_cast<float4 *>(records), counts, dkey, spans, big_list, big_count);
-    hipLaunchKernelGGL(k_count_big, dim3(1024), dim3(256), 0, s, reinterpret_cast<const float4 *>(records), vt, rs,
-                       g.n, counts, big_list, big_count);
+    if (R <= 0) return clear_one ? launch_fill_u32(clear_one, 0u, 1, s) : hipSuccess;
+    hipLaunchKernelGGL(k_preprocess, dim3((unsigned)((g.n + 255) / 256), 1u), dim3(256), 0, s, g, vt, T_cw, rs,
+                       reinterpret_cast<float4 *>(records), counts, dkey, spans, live, clear_one, clear, n_clear);
     return hipGetLastError();
 }
 
