@@ -93,8 +93,11 @@ __global__ void k_covis_finalize(const unsigned long long *__restrict__ counts, 
     if (j == 0 && count_out) count_out[i] = (int64_t)ci;
 }
 
-// Radix selection of the lower median of the positive depths of each view, 8 bits per
-// round from the top: positive float bit patterns order like the floats.
+// Radix selection of the lower median of the positive depths of each view, 11, 11 and 10 bits
+// from the top: positive float bit patterns order like the floats.  Each round is one histogram
+// over the pixels, and every workgroup of the next takes the previous round's choice from its
+// histogram itself: launches of a few us bound this (2 x 960x640: four rounds of 8 bits with a
+// launch for each choice 84 us, 35 us now).
 struct MedianState {
     uint32_t prefix;  // bits selected so far
     uint32_t rank;    // rank of the median among the values that match the prefix
@@ -102,15 +105,62 @@ struct MedianState {
     uint32_t pad;
 };
 
-__global__ void __launch_bounds__(256)
-k_median_hist(ViewTable vt, const float *__restrict__ depth, int round, const MedianState *__restrict__ st,
-              uint32_t *__restrict__ hist) {
-    __shared__ uint32_t h[256];
-    const int v = blockIdx.y;
-    h[threadIdx.x] = 0u;
+constexpr int kMedianBits = 11, kMedianBins = 1 << kMedianBits, kMedianRounds = 3;
+constexpr int kMedianBlock = 256, kMedianPer = kMedianBins / kMedianBlock;
+__host__ __device__ constexpr int median_shift(int round) { return round == 2 ? 0 : 32 - kMedianBits * (round + 1); }
+
+// The state after round `round` from the one before it and the round's histogram, for every lane.
+__device__ inline MedianState median_choose(int round, const MedianState *__restrict__ st,
+                                            const uint32_t *__restrict__ hist) {
+    __shared__ uint32_t waves[kMedianBlock / kWave];
+    __shared__ MedianState chosen;
+    uint32_t h[kMedianPer], sum = 0u;
+#pragma unroll
+    for (int k = 0; k < kMedianPer; ++k) {
+        h[k] = hist[threadIdx.x * kMedianPer + k];
+        sum += h[k];
+    }
+    const uint32_t inc = wave_inclusive_scan(sum);
+    if (lane_id() == kWave - 1) waves[threadIdx.x / kWave] = inc;
     __syncthreads();
-    const int shift = 24 - 8 * round;
-    const uint32_t prefix = round ? st[v].prefix : 0u;
+    uint32_t below = inc - sum, n = 0u;
+#pragma unroll
+    for (int w = 0; w < kMedianBlock / kWave; ++w) {
+        below += w < (int)(threadIdx.x / kWave) ? waves[w] : 0u;
+        n += waves[w];
+    }
+    MedianState s = {0u, n ? (n - 1u) / 2u : 0u, n, 0u};
+    if (round > 0) s = *st;
+    if (threadIdx.x == 0) chosen = s;
+    __syncthreads();
+    if (s.rank >= below && s.rank < below + sum) {  // one lane, if there is a value at all
+        s.rank -= below;
+        int b = 0;
+        while (s.rank >= h[b]) s.rank -= h[b++];
+        s.prefix = (s.prefix << (median_shift(round - 1) - median_shift(round))) | (uint32_t)(threadIdx.x * kMedianPer + b);
+        chosen = s;
+    }
+    __syncthreads();
+    return chosen;
+}
+
+// st, hist: [rounds][views]; the state after round r is written by round r + 1.
+__global__ void __launch_bounds__(kMedianBlock)
+k_median_hist(ViewTable vt, const float *__restrict__ depth, int round, MedianState *__restrict__ st,
+              uint32_t *__restrict__ hist) {
+    __shared__ uint32_t h[kMedianBins];
+    const int v = blockIdx.y, V = vt.n_views;
+    MedianState s = {};
+    if (round > 0) {
+        const int64_t before = (int64_t)(round - 1) * V + v;
+        s = median_choose(round - 1, st + before - V, hist + before * kMedianBins);
+        if (blockIdx.x == 0 && threadIdx.x == 0) st[before] = s;
+        if (s.n == 0u) return;  // block-uniform
+    }
+    for (int b = threadIdx.x; b < kMedianBins; b += kMedianBlock) h[b] = 0u;
+    __syncthreads();
+    const int shift = median_shift(round);
+    const uint32_t bins = (1u << (round ? median_shift(round - 1) - shift : kMedianBits)) - 1u;
     const int64_t np = (int64_t)vt.width[v] * vt.height[v];
     const float *d = depth + vt.pix_off[v];
     // Uniform trip count per wave, so the ballots below see every lane.
@@ -119,9 +169,13 @@ k_median_hist(ViewTable vt, const float *__restrict__ depth, int round, const Me
         const int64_t e = e0 + threadIdx.x;
         const float x = e < np ? d[e] : 0.0f;
         const uint32_t b = __float_as_uint(x);
-        const bool valid = x > 0.0f && (round == 0 || (b >> (shift + 8)) == prefix);
-        const uint32_t bin = (b >> shift) & 255u;
-        // Depths cluster in few bins: one LDS atomic per distinct bin of the wave.
+        const bool valid = x > 0.0f && (round == 0 || (b >> median_shift(round - 1)) == s.prefix);
+        const uint32_t bin = (b >> shift) & bins;
+        if (round > 0) {  // mantissa bits: spread over the bins
+            if (valid) atomicAdd(&h[bin], 1u);
+            continue;
+        }
+        // Depths cluster in few top bins: one LDS atomic per distinct bin of the wave.
         uint64_t active = ballot(valid);
         while (active) {
             const int leader = __ffsll((unsigned long long)active) - 1;
@@ -132,34 +186,17 @@ k_median_hist(ViewTable vt, const float *__restrict__ depth, int round, const Me
         }
     }
     __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(hist + v * 256 + threadIdx.x, h[threadIdx.x]);
+    uint32_t *out = hist + ((int64_t)round * V + v) * kMedianBins;
+    for (int b = threadIdx.x; b < kMedianBins; b += kMedianBlock)
+        if (h[b]) atomicAdd(out + b, h[b]);
 }
 
-__global__ void __launch_bounds__(256)
-k_median_select(int round, MedianState *__restrict__ st, uint32_t *__restrict__ hist, float *__restrict__ out) {
-    __shared__ uint32_t h[256];
-    const int v = blockIdx.x;
-    h[threadIdx.x] = hist[v * 256 + threadIdx.x];
-    hist[v * 256 + threadIdx.x] = 0u;  // cleared for the next round
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    MedianState s = st[v];
-    if (round == 0) {
-        uint32_t n = 0u;
-        for (int b = 0; b < 256; ++b) n += h[b];
-        s.n = n;
-        s.rank = n ? (n - 1u) / 2u : 0u;
-        s.prefix = 0u;
-    }
-    if (s.n != 0u) {
-        uint32_t below = 0u;
-        int b = 0;
-        while (b < 255 && below + h[b] <= s.rank) below += h[b++];
-        s.rank -= below;
-        s.prefix = (s.prefix << 8) | (uint32_t)b;
-    }
-    st[v] = s;
-    if (round == 3) out[v] = s.n ? __uint_as_float(s.prefix) : 0.0f;
+__global__ void __launch_bounds__(kMedianBlock)
+k_median_finish(const MedianState *__restrict__ st, const uint32_t *__restrict__ hist, float *__restrict__ out) {
+    const int v = blockIdx.x, V = gridDim.x;
+    const int64_t last = (int64_t)(kMedianRounds - 1) * V + v;
+    const MedianState s = median_choose(kMedianRounds - 1, st + last - V, hist + last * kMedianBins);
+    if (threadIdx.x == 0) out[v] = s.n ? __uint_as_float(s.prefix) : 0.0f;
 }
 
 }  // namespace
@@ -188,22 +225,21 @@ hipError_t launch_covisibility(const uint8_t *visible, int64_t n, int V, const F
     return hipGetLastError();
 }
 
-int64_t median_scratch_words(int V) { return (int64_t)V * (256 + 4); }
+int64_t median_scratch_words(int V) { return (int64_t)V * kMedianRounds * (kMedianBins + 4); }
 
 hipError_t launch_median_depth(const ViewTable &vt, const float *depth, uint32_t *scratch, float *out,
                                hipStream_t s) {
     const int V = vt.n_views;
     uint32_t *hist = scratch;
-    MedianState *st = reinterpret_cast<MedianState *>(scratch + (int64_t)V * 256);
-    hipError_t e = launch_fill_u32(scratch, 0u, median_scratch_words(V), s);
+    MedianState *st = reinterpret_cast<MedianState *>(scratch + (int64_t)V * kMedianRounds * kMedianBins);
+    hipError_t e = launch_fill_u32(hist, 0u, (int64_t)V * kMedianRounds * kMedianBins, s);
     if (e != hipSuccess) return e;
     int64_t maxp = 1;
     for (int v = 0; v < V; ++v) maxp = std::max<int64_t>(maxp, (int64_t)vt.width[v] * vt.height[v]);
-    const unsigned bx = (unsigned)std::min<int64_t>(256, (maxp + 255) / 256);
-    for (int round = 0; round < 4; ++round) {
-        hipLaunchKernelGGL(k_median_hist, dim3(bx, V), dim3(256), 0, s, vt, depth, round, st, hist);
-        hipLaunchKernelGGL(k_median_select, dim3(V), dim3(256), 0, s, round, st, hist, out);
-    }
+    const unsigned bx = (unsigned)std::min<int64_t>(256, (maxp + kMedianBlock - 1) / kMedianBlock);
+    for (int round = 0; round < kMedianRounds; ++round)
+        hipLaunchKernelGGL(k_median_hist, dim3(bx, V), dim3(kMedianBlock), 0, s, vt, depth, round, st, hist);
+    hipLaunchKernelGGL(k_median_finish, dim3(V), dim3(kMedianBlock), 0, s, st, hist, out);
     return hipGetLastError();
 }
 
