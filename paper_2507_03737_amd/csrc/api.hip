@@ -218,7 +218,7 @@ hipError_t ensure_records(gspm_ctx *c, int64_t R, int digit_bits) {
     if ((e = grow(c->offsets, 4 * w))) return e;
     if ((e = grow(c->spans, 16 * w))) return e;
     if ((e = grow(c->hist, 4 * radix_hist_words(w, digit_bits)))) return e;
-    if ((e = grow(c->scan_part, 4 * kScanMaxBlocks))) return e;
+    if ((e = grow(c->scan_part, 4 * (kScanMaxBlocks + scan_status_words(w))))) return e;
     if ((e = grow(c->misc, 256))) return e;
     return hipSuccess;
 }
@@ -387,10 +387,11 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
     PhaseTimer t_pre(ctx, hs, GSPM_PHASE_PREPROCESS);
     const int64_t n_per_view = g->n > 0 ? g->n : 1;
     uint64_t *live = static_cast<uint64_t *>(ctx->big.p);
-    uint64_t *large = live + 2 * P.vt.n_views * live_waves(n_per_view);  // of the records in depth order
+    uint8_t *large = reinterpret_cast<uint8_t *>(live + 2 * P.vt.n_views * live_waves(n_per_view));  // in depth order
     GSPM_HIP(launch_preprocess(*g, P.vt, views->T_cw, P.rs, records, counts, static_cast<uint32_t *>(ctx->dkey.p),
                                static_cast<uint4 *>(ctx->spans.p), live, &hdr->sort_stall, hist, radix_total_words(db),
-                               hs));
+                               part + kScanMaxBlocks,
+                               R <= 0 ? 0 : scan_status_words(R), hs));
     t_pre.stop();
     // Device-side counts: total[0] tile pairs, total[1] live records.
     uint32_t *n_live = total + 1;
@@ -414,9 +415,9 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
         // 3. Offsets of each live record's tile pairs, in depth order.
         // The sorted depth keys are no longer needed: their buffer receives the pair counts
         // in depth order, unpacked (or gathered) once by the scan.
-        GSPM_HIP(launch_scan_indirect(counts, static_cast<uint32_t *>(ctx->dval_s.p), R,
-                                      static_cast<uint32_t *>(ctx->offsets.p), total, part, hs, n_live, pack,
-                                      static_cast<uint32_t *>(ctx->dkey_s.p)));
+        GSPM_HIP(launch_scan_offsets(counts, static_cast<uint32_t *>(ctx->dval_s.p), R,
+                                     static_cast<uint32_t *>(ctx->offsets.p), total, part, &hdr->sort_stall, hs, n_live,
+                                     pack, static_cast<uint32_t *>(ctx->dkey_s.p), large));
     } else {
         GSPM_HIP(launch_fill_u32(total, 0u, 2, hs));
     }

@@ -21,11 +21,20 @@ constexpr int kScanBlock = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanBlock * kScanItems;
 
-// Pair count of the p-th record of idx (with packed: its top bits, unless saturated).
-__device__ inline uint32_t load_count(const uint32_t *counts, const uint32_t *idx, int64_t p, bool packed) {
-    const uint32_t v = idx[p], c = v >> kPackShift;
+// Pair count of a record, with packed carried in the top bits of its index (unless saturated).
+__device__ inline uint32_t record_count(const uint32_t *counts, uint32_t v, bool packed) {
+    const uint32_t c = v >> kPackShift;
     if (packed && c < kPackCountMax) return c;
     return counts[packed ? v & kPackMask : v] & ~kBigCount;
+}
+
+// One bit per record with more than kBigRecord pairs.
+__device__ inline uint8_t large_bits(const uint32_t (&v)[kScanItems]) {
+    static_assert(kScanItems == 8, "one byte");
+    uint32_t bits = 0u;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) bits |= (v[k] > kBigRecord ? 1u : 0u) << k;
+    return (uint8_t)bits;
 }
 
 // Elements per block of the device-wide scans: a multiple of kScanItems, so that every
@@ -75,7 +84,7 @@ k_scan_reduce(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ 
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
             const int64_t p = base + k * kScanBlock + threadIdx.x;
-            c[k] = p < b1 ? load_count(counts, idx, p, packed) : 0u;
+            c[k] = p < b1 ? record_count(counts, idx[p], packed) : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
@@ -114,7 +123,8 @@ __device__ inline uint32_t partial_prefix(const uint32_t *__restrict__ part, int
 
 __global__ void __launch_bounds__(kScanBlock)
 k_scan_apply(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ n_dev, int64_t n_max,
-             const uint32_t *__restrict__ part, uint32_t *__restrict__ out, uint32_t *__restrict__ total) {
+             const uint32_t *__restrict__ part, uint32_t *__restrict__ out, uint32_t *__restrict__ total,
+             uint8_t *__restrict__ large) {
     __shared__ uint32_t lds[kScanBlock / kWave];
     const int64_t n = scan_n(n_dev, n_max);
     const int64_t chunk = scan_chunk(n);
@@ -141,6 +151,7 @@ k_scan_apply(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ n
         }
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) sum += v[k];
+        if (p0 < b1) large[p0 / 8] = large_bits(v);
         uint32_t tot;
         uint32_t pre = running + block_exclusive_scan(sum, lds, tot);
         uint32_t o[kScanItems];
@@ -508,11 +519,103 @@ k_radix_tile_prefix(uint32_t *__restrict__ tcount, int64_t tstride, const uint32
     if (threadIdx.x == 0) ghist[d] = running;
 }
 
-__device__ inline uint32_t load_status(const uint32_t *p) {
+template <typename W>
+__device__ inline W load_status(const W *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline void store_status(uint32_t *p, uint32_t v) {
+template <typename W>
+__device__ inline void store_status(W *p, W v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Offsets of the records' pairs in depth order in one launch, for windows of up to kScanSmall
+// records: block b publishes the sum of its kScanTile counts and adds up the earlier blocks' by
+// looking back, 64 of them at a time, as the sort's passes do (and as bounded).  Also
+// gathered[p], the counts in depth order, and large, a byte per thread.  Launches bound it: 300k
+// records 6.2 us against 9.0 with k_scan_reduce and k_scan_apply, 500k 9.2 against 10.8; for
+// 8M the walk back over 2000 blocks takes longer than the launch, 30 against 23 us.
+constexpr int64_t kScanSmall = 1 << 20;
+constexpr uint64_t kScanAgg = 1ull << 62, kScanInc = 2ull << 62;
+
+__global__ void __launch_bounds__(kScanBlock)
+k_scan_offsets(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ idx, const uint32_t *__restrict__ n_dev,
+               int64_t n_max, bool packed, uint64_t *__restrict__ status, uint32_t *__restrict__ stall,
+               uint32_t *__restrict__ gathered, uint32_t *__restrict__ offsets, uint8_t *__restrict__ large,
+               uint32_t *__restrict__ total) {
+    __shared__ uint32_t lds[kScanBlock / kWave];
+    __shared__ uint64_t earlier;
+    const int64_t n = scan_n(n_dev, n_max), p0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    const bool last = (int64_t)(blockIdx.x + 1) * kScanTile >= n;
+    if (blockIdx.x > 0 && (int64_t)blockIdx.x * kScanTile >= n) return;  // block-uniform
+    uint32_t v[kScanItems], sum = 0u;
+    const bool whole = p0 + kScanItems <= n;
+    if (whole && packed) {  // two 16-byte loads
+        const uint4 a = *reinterpret_cast<const uint4 *>(idx + p0), c = *reinterpret_cast<const uint4 *>(idx + p0 + 4);
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = c.x; v[5] = c.y; v[6] = c.z; v[7] = c.w;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) v[k] = record_count(counts, v[k], true);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k)
+            v[k] = p0 + k < n ? record_count(counts, idx[p0 + k], packed) : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) sum += v[k];
+    uint32_t tot;
+    uint32_t pre = block_exclusive_scan(sum, lds, tot);
+    if (threadIdx.x < kWave) {
+        const int lane = lane_id();
+        if (lane == 0) store_status(status + blockIdx.x, (blockIdx.x == 0 ? kScanInc : kScanAgg) | (uint64_t)tot);
+        uint64_t prefix = 0ull;
+        uint32_t spins = 0u;
+        for (int64_t j = (int64_t)blockIdx.x - 1; j >= 0;) {  // wave-uniform
+            const uint64_t w = j >= lane ? load_status(status + (j - lane)) : kScanInc;
+            const uint64_t ready = ballot((w >> 62) != 0ull), inc = ballot((w & kScanInc) != 0ull);
+            // The words up to the nearest inclusive one, all of them published.
+            const int stop = inc != 0ull ? (int)__builtin_ctzll(inc) : kWave - 1;
+            const uint64_t need = stop == kWave - 1 ? ~0ull : (1ull << (stop + 1)) - 1ull;
+            if ((ready & need) != need) {
+                if (++spins > kSortSpinLimit || load_status(stall) != 0u) {
+                    if (lane == 0) store_status(stall, 1u);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                continue;
+            }
+            uint64_t x = lane <= stop ? w & ~(kScanAgg | kScanInc) : 0ull;
+            for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
+            prefix += x;
+            if (inc != 0ull) break;
+            j -= kWave;
+        }
+        if (lane == 0) {
+            if (blockIdx.x > 0) store_status(status + blockIdx.x, kScanInc | (prefix + tot));
+            earlier = prefix;
+            if (last) *total = (uint32_t)prefix + tot;
+        }
+    }
+    __syncthreads();
+    pre += (uint32_t)earlier;
+    uint32_t o[kScanItems];
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        o[k] = pre;
+        pre += v[k];
+    }
+    if (p0 < n) large[p0 / 8] = large_bits(v);
+    if (whole) {
+        *reinterpret_cast<uint4 *>(gathered + p0) = make_uint4(v[0], v[1], v[2], v[3]);
+        *reinterpret_cast<uint4 *>(gathered + p0 + 4) = make_uint4(v[4], v[5], v[6], v[7]);
+        *reinterpret_cast<uint4 *>(offsets + p0) = make_uint4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<uint4 *>(offsets + p0 + 4) = make_uint4(o[4], o[5], o[6], o[7]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k)
+            if (p0 + k < n) {
+                gathered[p0 + k] = v[k];
+                offsets[p0 + k] = o[k];
+            }
+    }
 }
 
 template <int DB, int STEPS>
@@ -709,7 +812,7 @@ __device__ inline void emit_row(uint32_t *__restrict__ pkey, uint32_t *__restric
 }
 
 // One lane per record (in depth order; sorted_counts[p] is the pair count of sorted_rec[p]).
-// Records with many pairs are left to k_keygen_big.
+// Records with many pairs are left to emit_large.
 //
 // A wave's records are consecutive in depth order, so their pairs form one contiguous run
 // of the output.  The wave lists the tile rows of its records in LDS (output position,
@@ -719,28 +822,96 @@ __device__ inline void emit_row(uint32_t *__restrict__ pkey, uint32_t *__restric
 // window (a ballot and a prefix count), so every lane emits one pair per step whatever
 // the records' sizes and the stores are consecutive.  Records whose rows the counting pass
 // did not cache (more than kSpanRowsMax rows) are emitted by their own lane, row by row;
-// positions of large records are left to k_keygen_big.
+// positions of large records are left to emit_large.
 constexpr int kKeygenBlock = 256;
 constexpr int kKeygenWaves = kKeygenBlock / kWave;
 constexpr int kKeygenRows = kWave * (int)kSpanRowsMax;  // rows of one wave's records, at most
+// A block's LDS: the rows of its waves' records, or (the blocks that emit large records) a list.
+struct KeygenRows {
+    uint32_t pos[kKeygenWaves][kKeygenRows];   // first output position
+    uint32_t tile[kKeygenWaves][kKeygenRows];  // global tile id of the first tile
+    uint32_t rec[kKeygenWaves][kKeygenRows];   // record index
+    uint8_t len[kKeygenWaves][kKeygenRows];    // tiles (at most kBigRecord)
+    uint8_t starts[kKeygenWaves][kWave];       // rows starting at window position
+};
+constexpr uint32_t kLargeParts = 8, kLargeBits = kWave / kLargeParts;
+struct LargeList {
+    uint32_t pos[kKeygenBlock * kLargeBits];
+    uint32_t scan[kKeygenWaves];
+};
 
+// The pairs of the large records, one wave per record and one lane per tile row; block bb of
+// nbb.  A block takes bytes of the large bits a whole grid apart (large records are near, and
+// thus neighbours in depth order) and lists their records in LDS, so that its waves share them
+// evenly.
+__device__ void emit_large(LargeList &ls, const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask,
+                           const uint32_t *__restrict__ offsets, const float4 *__restrict__ rec, const RasterSettings &rs,
+                           int64_t n_live, int64_t n_per_view, const ViewTable &vt, uint32_t *__restrict__ pkey,
+                           uint32_t *__restrict__ pval, uint32_t cap, const uint8_t *__restrict__ large, uint32_t bb,
+                           uint32_t nbb) {
+    static_assert(kLargeBits == 8, "one byte");
+    const int lane = lane_id();
+    const uint32_t items = (uint32_t)((n_live + 7) / 8);
+    for (uint32_t i0 = bb; i0 < items; i0 += (uint32_t)kKeygenBlock * nbb) {
+        const uint32_t i = i0 + threadIdx.x * nbb;
+        uint32_t m = i < items ? (uint32_t)large[i] : 0u;
+        uint32_t n_list, k = block_exclusive_scan((uint32_t)__popc(m), ls.scan, n_list);
+        for (; m != 0u; m &= m - 1u) ls.pos[k++] = kLargeBits * i + (uint32_t)__builtin_ctz(m);
+        __syncthreads();
+        for (uint32_t q = threadIdx.x / kWave; q < n_list; q += kKeygenWaves) {
+            const uint32_t p = (uint32_t)__builtin_amdgcn_readfirstlane((int)ls.pos[q]);
+            const uint32_t r = sorted_rec[p] & rec_mask;
+            const int v = (int)(r / (uint32_t)n_per_view);
+            Footprint f;
+            if (!record_footprint(rec[4 * (int64_t)r], rec[4 * (int64_t)r + 1], rs.alpha_min, vt.width[v],
+                                  vt.height[v], f))
+                continue;  // wave-uniform
+            const int T = vt.tile, sh = __builtin_ctz((unsigned)vt.tile);
+            const uint32_t base = (uint32_t)vt.tile_off[v], tiles_x = (uint32_t)vt.tiles_x[v];
+            uint32_t k0 = offsets[p];
+            for (int ty0 = f.j0 >> sh; ty0 <= f.j1 >> sh; ty0 += kWave) {
+                const int ty = ty0 + lane;
+                int ta = 0, tb = -1;
+                if (ty <= f.j1 >> sh && !row_span(f, T, ty, ta, tb)) tb = ta - 1;
+                if (ty > f.j1 >> sh) tb = ta - 1;
+                const uint32_t len = (uint32_t)(tb - ta + 1);
+                const uint32_t inc = wave_inclusive_scan(len);
+                uint32_t kk = k0 + inc - len;
+                if (len) emit_row(pkey, pval, cap, kk, base, tiles_x, ty, ta, tb, r);
+                k0 += __shfl(inc, kWave - 1, kWave);
+            }
+        }
+        __syncthreads();  // the list is read before the next round writes it
+    }
+}
+
+// ROWS, LARGE: whether the launch holds blocks for the ordinary and for the large records.
+template <bool ROWS, bool LARGE>
 __global__ void __launch_bounds__(kKeygenBlock)
 k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint32_t *__restrict__ sorted_counts,
          const uint32_t *__restrict__ offsets, const float4 *__restrict__ rec, const uint4 *__restrict__ spans,
          RasterSettings rs, int64_t n_records, int64_t n_per_view, ViewTable vt, uint32_t *__restrict__ pkey,
          uint32_t *__restrict__ pval, FrameHeader *__restrict__ hdr, uint32_t cap,
-         const uint32_t *__restrict__ total, uint64_t *__restrict__ large, const uint32_t *__restrict__ n_dev,
-         uint2 *__restrict__ ranges, KeygenClears clr) {
-    __shared__ uint32_t row_pos[kKeygenWaves][kKeygenRows];   // first output position
-    __shared__ uint32_t row_tile[kKeygenWaves][kKeygenRows];  // global tile id of the first tile
-    __shared__ uint32_t row_rec[kKeygenWaves][kKeygenRows];   // record index
-    __shared__ uint8_t row_len[kKeygenWaves][kKeygenRows];    // tiles (at most kBigRecord)
-    __shared__ uint8_t starts[kKeygenWaves][kWave];          // rows starting at window position
+         const uint32_t *__restrict__ total, const uint8_t *__restrict__ large, const uint32_t *__restrict__ n_dev,
+         uint2 *__restrict__ ranges, KeygenClears clr, uint32_t nb) {
+    __shared__ union {
+        KeygenRows rows;
+        LargeList large;
+    } lds;
+    if (LARGE && (!ROWS || blockIdx.x >= nb))  // the last blocks emit the large records
+        return emit_large(lds.large, sorted_rec, rec_mask, offsets, rec, rs, scan_n(n_dev, n_records), n_per_view, vt, pkey,
+                          pval, cap, large, blockIdx.x - nb, gridDim.x - nb);
+    if (!ROWS) return;
+    auto &row_pos = lds.rows.pos;
+    auto &row_tile = lds.rows.tile;
+    auto &row_rec = lds.rows.rec;
+    auto &row_len = lds.rows.len;
+    auto &starts = lds.rows.starts;
     const int wid = threadIdx.x / kWave, lane = lane_id();
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     // Empty tile ranges, for the tile sort's last pass to narrow (here to save a launch).
     // The per-tile work that the forward's waves raise starts at 0.
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    const int64_t step = (int64_t)nb * blockDim.x;
     for (int64_t t = p; t < clr.n_tiles; t += step) {
         ranges[t] = make_uint2(0xffffffffu, 0u);
         clr.twork[t] = 0u;
@@ -777,9 +948,6 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
         k = offsets[p];
     }
     const bool big = c > kBigRecord;
-    // For k_keygen_big (a queue would cost an atomic on one address per wave).
-    const uint64_t big_lanes = ballot(big);
-    if (lane == 0 && act) large[p / kWave] = big_lanes;
     const bool own = act && c != 0u && !big;
     int v = 0, ty0 = 0, nr = 0;
     uint32_t base = 0, tiles_x = 0;
@@ -864,52 +1032,6 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
     }
 }
 
-// The pairs of the large records, one wave per record and one lane per tile row.  A block takes
-// eighths of the emitter's words a whole grid apart (large records are near, and thus neighbours in
-// depth order) and lists their records in LDS, so that its waves share them evenly.
-__global__ void __launch_bounds__(256)
-k_keygen_big(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint32_t *__restrict__ offsets,
-             const float4 *__restrict__ rec, RasterSettings rs, int64_t n_records, int64_t n_per_view, ViewTable vt,
-             uint32_t *__restrict__ pkey, uint32_t *__restrict__ pval, uint32_t cap,
-             const uint64_t *__restrict__ large, const uint32_t *__restrict__ n_dev) {
-    constexpr uint32_t kParts = 8, kBits = kWave / kParts;
-    __shared__ uint32_t list[256 * kBits];
-    __shared__ uint32_t lds[256 / kWave];
-    const int lane = lane_id();
-    const uint32_t items = (uint32_t)((scan_n(n_dev, n_records) + kWave - 1) / kWave) * kParts;
-    for (uint32_t i0 = blockIdx.x; i0 < items; i0 += 256u * gridDim.x) {
-        const uint32_t i = i0 + threadIdx.x * gridDim.x;
-        uint32_t m = i < items ? (uint32_t)(large[i / kParts] >> (kBits * (i % kParts))) & ((1u << kBits) - 1u) : 0u;
-        uint32_t n_list, k = block_exclusive_scan((uint32_t)__popc(m), lds, n_list);
-        for (; m != 0u; m &= m - 1u) list[k++] = kBits * i + (uint32_t)__builtin_ctz(m);
-        __syncthreads();
-        for (uint32_t q = threadIdx.x / kWave; q < n_list; q += 256 / kWave) {
-            const uint32_t p = (uint32_t)__builtin_amdgcn_readfirstlane((int)list[q]);
-            const uint32_t r = sorted_rec[p] & rec_mask;
-            const int v = (int)(r / (uint32_t)n_per_view);
-            Footprint f;
-            if (!record_footprint(rec[4 * (int64_t)r], rec[4 * (int64_t)r + 1], rs.alpha_min, vt.width[v],
-                                  vt.height[v], f))
-                continue;  // wave-uniform
-            const int T = vt.tile, sh = __builtin_ctz((unsigned)vt.tile);
-            const uint32_t base = (uint32_t)vt.tile_off[v], tiles_x = (uint32_t)vt.tiles_x[v];
-            uint32_t k0 = offsets[p];
-            for (int ty0 = f.j0 >> sh; ty0 <= f.j1 >> sh; ty0 += kWave) {
-                const int ty = ty0 + lane;
-                int ta = 0, tb = -1;
-                if (ty <= f.j1 >> sh && !row_span(f, T, ty, ta, tb)) tb = ta - 1;
-                if (ty > f.j1 >> sh) tb = ta - 1;
-                const uint32_t len = (uint32_t)(tb - ta + 1);
-                const uint32_t inc = wave_inclusive_scan(len);
-                uint32_t kk = k0 + inc - len;
-                if (len) emit_row(pkey, pval, cap, kk, base, tiles_x, ty, ta, tb, r);
-                k0 += __shfl(inc, kWave - 1, kWave);
-            }
-        }
-        __syncthreads();  // the list is read before the next round writes it
-    }
-}
-
 __global__ void __launch_bounds__(256) k_sum_u64(const uint32_t *__restrict__ x, int64_t n,
                                                 unsigned long long *__restrict__ out) {
     unsigned long long acc = 0;
@@ -932,20 +1054,23 @@ hipError_t launch_sum_u64(const uint32_t *x, int64_t n, unsigned long long *out,
 
 // ------------------------------- host wrappers ----------------------------------------
 
-// One block per tile of kScanTile elements (up to kScanMaxBlocks): every block then does
-// one round of loads, scan and stores, where fewer blocks would each wait on several.
-static int64_t scan_blocks(int64_t n) {
-    int64_t nb = (n + kScanTile - 1) / kScanTile;
-    if (nb > kScanMaxBlocks) nb = kScanMaxBlocks;
-    return nb < 1 ? 1 : nb;
-}
+int64_t scan_status_words(int64_t n) { return 2 * ((std::min(n, kScanSmall) + kScanTile - 1) / kScanTile); }
 
-hipError_t launch_scan_indirect(const uint32_t *counts, const uint32_t *idx, int64_t n, uint32_t *offsets,
-                                uint32_t *total, uint32_t *part, hipStream_t s, const uint32_t *n_dev, bool packed,
-                                uint32_t *gathered) {
-    const unsigned nb = (unsigned)scan_blocks(n);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kScanBlock), 0, s, counts, idx, n_dev, n, packed, part, gathered);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(kScanBlock), 0, s, gathered, n_dev, n, part, offsets, total);
+hipError_t launch_scan_offsets(const uint32_t *counts, const uint32_t *idx, int64_t n, uint32_t *offsets,
+                               uint32_t *total, uint32_t *part, uint32_t *stall, hipStream_t s, const uint32_t *n_dev,
+                               bool packed, uint32_t *gathered, uint8_t *large) {
+    if (n <= 0) return hipSuccess;
+    // One block per tile of kScanTile elements: every block then does one round of loads, scan
+    // and stores, where fewer blocks would each wait on several.
+    const int64_t nb = (n + kScanTile - 1) / kScanTile;
+    if (n <= kScanSmall) {
+        hipLaunchKernelGGL(k_scan_offsets, dim3((unsigned)nb), dim3(kScanBlock), 0, s, counts, idx, n_dev, n, packed,
+                           reinterpret_cast<uint64_t *>(part + kScanMaxBlocks), stall, gathered, offsets, large, total);
+        return hipGetLastError();
+    }
+    const unsigned blocks = (unsigned)std::min<int64_t>(nb, kScanMaxBlocks);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(blocks), dim3(kScanBlock), 0, s, counts, idx, n_dev, n, packed, part, gathered);
+    hipLaunchKernelGGL(k_scan_apply, dim3(blocks), dim3(kScanBlock), 0, s, gathered, n_dev, n, part, offsets, total, large);
     return hipGetLastError();
 }
 
@@ -1071,17 +1196,30 @@ hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const ui
                          const uint32_t *offsets, const float *records, const uint4 *spans, const RasterSettings &rs,
                          int64_t n_records, int64_t n_per_view,
                          const ViewTable &vt, uint32_t *pkey, uint32_t *pval, FrameHeader *hdr, uint32_t capacity,
-                         const uint32_t *total, uint64_t *large, const uint32_t *n_dev, uint2 *ranges,
+                         const uint32_t *total, const uint8_t *large, const uint32_t *n_dev, uint2 *ranges,
                          const KeygenClears &clr, hipStream_t s) {
     const float4 *rec = reinterpret_cast<const float4 *>(records);
     // Enough blocks for the records, and for the clearing where there are few of them.
     const int64_t clears = clr.n_tiles + clr.n_visible + clr.n_wmask;
     const int64_t nb = std::max<int64_t>(std::max<int64_t>(1, (n_records + 255) / 256), std::min<int64_t>(512, clears / 2048));
-    hipLaunchKernelGGL(k_keygen, dim3((unsigned)nb), dim3(256), 0, s, sorted_rec, rec_mask, sorted_counts, offsets, rec,
-                       spans, rs, n_records, n_per_view, vt, pkey, pval, hdr, capacity, total, large, n_dev, ranges, clr);
-    if (n_records > 0)
-        hipLaunchKernelGGL(k_keygen_big, dim3(1024), dim3(256), 0, s, sorted_rec, rec_mask, offsets, rec, rs, n_records,
-                           n_per_view, vt, pkey, pval, capacity, large, n_dev);
+    const int64_t nbig = n_records > 0 ? std::min<int64_t>(1024, std::max<int64_t>(64, n_records / 512)) : 0;
+    // One launch for both where launches count (500k records: 45 us against 55), two where the
+    // large records' blocks only lengthen the end (8M: 188 us against 191, 48M: 1.46 against 1.48 ms).
+    const bool together = n_records <= kScanSmall;
+    // (With the large records' code the kernel needs 80 registers, without it 60.)
+    auto launch = [&](auto kernel, int64_t rows, int64_t larges) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(rows + larges)), dim3(kKeygenBlock), 0, s, sorted_rec, rec_mask,
+                           sorted_counts, offsets, rec, spans, rs, n_records, n_per_view, vt, pkey, pval, hdr, capacity,
+                           total, large, n_dev, ranges, clr, (uint32_t)rows);
+    };
+    if (nbig == 0) {
+        launch(k_keygen<true, false>, nb, 0);
+    } else if (together) {
+        launch(k_keygen<true, true>, nb, nbig);
+    } else {
+        launch(k_keygen<true, false>, nb, 0);
+        launch(k_keygen<false, true>, 0, nbig);
+    }
     return hipGetLastError();
 }
 

@@ -408,14 +408,14 @@ hipError_t launch_fill_f32(float *p, float value, int64_t n, hipStream_t s);
 // with pairs in spans [N V].  Per view and 64 consecutive Gaussians (a segment), a word of live
 // says which have pairs (counts and dkey hold nothing for the others), and after all these
 // words as many say which of them are large: these have counts = kBigCount until
-// launch_compact has counted them.  clear_one (may be NULL) and clear[n_clear] are zeroed in
-// the same launch.
+// launch_compact has counted them.  clear_one (may be NULL), clear[n_clear] and
+// clear2[n_clear2] are zeroed in the same launch.
 constexpr uint32_t kBigCount = 1u << 31;  // a large record's count: this bit, and the count below it
 __host__ __device__ inline int64_t live_waves(int64_t n) { return (n + kWave - 1) / kWave; }
 hipError_t launch_preprocess(const gspm_gaussians &g, const ViewTable &vt, const float *T_cw,
                              const RasterSettings &rs, float *records, uint32_t *counts,
                              uint32_t *dkey, uint4 *spans, uint64_t *live, uint32_t *clear_one, uint32_t *clear,
-                             int n_clear, hipStream_t s);
+                             int n_clear, uint32_t *clear2, int64_t n_clear2, hipStream_t s);
 
 // A window of at most 2^kPackShift records carries each live record through the depth sort
 // as its index with its pair count in the top bits, so that the pair-offset scan reads
@@ -426,11 +426,14 @@ constexpr uint32_t kPackMask = (1u << kPackShift) - 1u;
 constexpr uint32_t kPackCountMax = (1u << (32 - kPackShift)) - 1u;
 
 // Exclusive scan for p < min(*n_dev, n) of counts[idx[p]] or, with packed, of the pair count
-// packed in idx[p] (see kPackShift), which also go to gathered[p].  Writes offsets[p] and the
-// total to *total.  part: kScanMaxBlocks words of scratch.
-hipError_t launch_scan_indirect(const uint32_t *counts, const uint32_t *idx, int64_t n,
-                                uint32_t *offsets, uint32_t *total, uint32_t *part, hipStream_t s,
-                                const uint32_t *n_dev, bool packed, uint32_t *gathered);
+// packed in idx[p] (see kPackShift), which also go to gathered[p].  Writes offsets[p], the total
+// to *total, and to large a bit per p for counts above kBigRecord.  part: kScanMaxBlocks words of
+// scratch and then scan_status_words(n) that the caller clears (launch_preprocess does).
+// *stall as for radix_sort.
+int64_t scan_status_words(int64_t n);
+hipError_t launch_scan_offsets(const uint32_t *counts, const uint32_t *idx, int64_t n, uint32_t *offsets,
+                               uint32_t *total, uint32_t *part, uint32_t *stall, hipStream_t s, const uint32_t *n_dev,
+                               bool packed, uint32_t *gathered, uint8_t *large);
 
 // Compacts (depth key, record index) of the records that live marks, in record order, and
 // writes their number to *n_live; with pack, the value also carries the pair count (see
@@ -471,8 +474,7 @@ struct KeygenClears {
 };
 
 // Emits the (global tile, record) pairs of every record in depth order.  Records with more than
-// kBigRecord pairs are marked in large (one word per 64 sorted records) and emitted by whole
-// waves.  records: the projected records (for the support footprint of records whose spans are not
+// kBigRecord pairs (large, see launch_scan_offsets) are emitted by whole waves.  records: the projected records (for the support footprint of records whose spans are not
 // cached in spans).  It also fills ranges [n_tiles] with the empty range (0xffffffff, 0) that the
 // tile sort's last pass narrows.  rec_mask: kPackMask if sorted_rec carries packed counts,
 // else all ones.
@@ -480,7 +482,7 @@ hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const ui
                          const uint32_t *offsets, const float *records, const uint4 *spans, const RasterSettings &rs,
                          int64_t n_records, int64_t n_per_view,
                          const ViewTable &vt, uint32_t *pkey, uint32_t *pval, FrameHeader *hdr,
-                         uint32_t capacity, const uint32_t *total, uint64_t *large, const uint32_t *n_dev,
+                         uint32_t capacity, const uint32_t *total, const uint8_t *large, const uint32_t *n_dev,
                          uint2 *ranges, const KeygenClears &clr, hipStream_t s);
 
 hipError_t launch_sum_u64(const uint32_t *x, int64_t n, unsigned long long *out, hipStream_t s);

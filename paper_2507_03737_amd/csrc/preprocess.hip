@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(256)
 k_preprocess(gspm_gaussians G, ViewTable vt, const float *__restrict__ T_cw, RasterSettings rs,
              float4 *__restrict__ rec, uint32_t *__restrict__ counts, uint32_t *__restrict__ dkey,
              uint4 *__restrict__ spans, uint64_t *__restrict__ live, uint32_t *__restrict__ clear_one,
-             uint32_t *__restrict__ clear, int n_clear) {
+             uint32_t *__restrict__ clear, int n_clear, uint32_t *__restrict__ clear2, int64_t n_clear2) {
     // One thread per Gaussian looping over the views: the view-independent part of the
     // projection is computed once.
     const int64_t n = G.n;
@@ -135,6 +135,7 @@ k_preprocess(gspm_gaussians G, ViewTable vt, const float *__restrict__ T_cw, Ras
         if (threadIdx.x == 0 && clear_one) *clear_one = 0u;
         for (int i = threadIdx.x; i < n_clear; i += blockDim.x) clear[i] = 0u;
     }
+    for (int64_t i = g; i < n_clear2; i += (int64_t)gridDim.x * blockDim.x) clear2[i] = 0u;
     Proj P;
     const bool framed = g < n && gaussian_frame(G, g, n, P);
     for (int v = 0; v < vt.n_views; ++v) {
@@ -532,11 +533,11 @@ hipError_t launch_fill_f32(float *p, float value, int64_t n, hipStream_t s) {
 hipError_t launch_preprocess(const gspm_gaussians &g, const ViewTable &vt, const float *T_cw,
                              const RasterSettings &rs, float *records, uint32_t *counts,
                              uint32_t *dkey, uint4 *spans, uint64_t *live, uint32_t *clear_one, uint32_t *clear,
-                             int n_clear, hipStream_t s) {
+                             int n_clear, uint32_t *clear2, int64_t n_clear2, hipStream_t s) {
     const int64_t R = g.n * vt.n_views;
     if (R <= 0) return clear_one ? launch_fill_u32(clear_one, 0u, 1, s) : hipSuccess;
     hipLaunchKernelGGL(k_preprocess, dim3((unsigned)((g.n + 255) / 256), 1u), dim3(256), 0, s, g, vt, T_cw, rs,
-                       reinterpret_cast<float4 *>(records), counts, dkey, spans, live, clear_one, clear, n_clear);
+                       reinterpret_cast<float4 *>(records), counts, dkey, spans, live, clear_one, clear, n_clear, clear2, n_clear2);
     return hipGetLastError();
 }
 
