@@ -616,9 +616,9 @@ def main():
     if cnt is not None and "valu_insts_per_launch" in cnt:
         roof["valu_issue_frac"] = cnt["valu_insts_per_launch"] / (ph_ms[dominant] * 1e-3) / cnt["valu_issue_peak_per_s"]
 
-    # At one pixel per lane the backward sums each record's values over a wave's pixels row by
-    # row; the same step with the cross-lane reduce-scatter instead, for comparison (same
-    # shape, same inputs).
+    # At one pixel per lane the backward sums each record's values over a wave's pixels on
+    # the matrix cores; the same step with the cross-lane reduce-scatter instead, for
+    # comparison (same shape, same inputs).
     bwd_forms = None
     if cfg.pixels_per_lane == 1:
         rast.cfg.bwd_lane_reduce = 1
@@ -628,7 +628,7 @@ def main():
         rast.ctx.timing(False)
         step.check()
         rast.cfg.bwd_lane_reduce = 0
-        bwd_forms = {"row_sums": {"raster_bwd_ms": ph_ms["raster_bwd"], "step_ms": ms_batched},
+        bwd_forms = {"matrix_cores": {"raster_bwd_ms": ph_ms["raster_bwd"], "step_ms": ms_batched},
                      "lane_reduce_scatter": {"raster_bwd_ms": ph_lane["raster_bwd"][0] / max(1, ph_lane["raster_bwd"][1]),
                                              "step_ms": ms_lane}}
         log(f"[bench] backward with the lane reduce-scatter: {bwd_forms['lane_reduce_scatter']['raster_bwd_ms']:.3f} ms")
@@ -688,7 +688,7 @@ def main():
             "pixels_per_lane": cfg.pixels_per_lane, "sort_digit_bits": cfg.sort_digit_bits,
             "autotuned": tuned is not None,
             "patch": 8, "loss_alpha": 0.98, "pointmap_frame": "camera",
-            "bwd_reduction": ("row sums: eight records of a wave at a time, a lane per record and row of pixels "
+            "bwd_reduction": ("matrix cores: each wave's per-record sums as v_mfma_f32_4x4x1_16b_f32 products, 16 records at a time "
                               "(the cross-lane DPP reduce-scatter form is timed beside it)"
                               if cfg.pixels_per_lane == 1 else "cross-lane DPP reduce-scatter"),
         },

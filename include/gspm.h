@@ -112,9 +112,9 @@ typedef struct {
     int32_t count_work;      /* nonzero: the forward also counts each pixel's contributing
                                 fragments, which gspm_frame_work reports [0] */
     int32_t bwd_lane_reduce; /* at one pixel per lane, the backward sums each record's
-                                values over a wave's pixels row by row, eight records at a
-                                time, in independent waves (0) or with a cross-lane
-                                reduce-scatter in workgroups (nonzero), the form it
+                                values over a wave's pixels with the matrix cores, in
+                                independent waves (0), or with a cross-lane reduce-scatter
+                                in workgroups (nonzero), the form it
                                 always uses at 2 and 4 pixels per lane; the results agree
                                 to float rounding [0] */
     int32_t grads_overwrite; /* nonzero: gspm_render_backward and gspm_pose_backward write the

@@ -32,7 +32,7 @@ struct RasterSettings {
     int32_t frame;  // 0 world, 1 camera, 2 depth back-projection
     int32_t mark_visible;
     int32_t count_work;  // the forward writes each pixel's contributing-fragment count
-    int32_t bwd_lane_reduce;  // one pixel per lane: reduce-scatter in workgroups instead of row sums
+    int32_t bwd_lane_reduce;  // one pixel per lane: reduce-scatter in workgroups instead of the matrix cores
     int32_t grads_overwrite;  // the backward writes the gradients instead of adding them
 };
 

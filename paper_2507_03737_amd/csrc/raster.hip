@@ -29,8 +29,8 @@
 // all fragments (from the forward's outputs) and each walked fragment subtracts its share.
 // Per record the wave needs up to 13 sums over its pixels: the moments of alpha dL/dalpha
 // over the pixel offsets (from which the mean, conic and opacity gradients follow) and the
-// colour, depth and point sums.  With one pixel per lane the wave forms them for 8 records
-// at a time, a lane per record and row of pixels; with several pixels per lane each lane
+// colour, depth and point sums.  With one pixel per lane the matrix cores form them for 16
+// records at a time; with several pixels per lane each lane
 // adds its pixels' contributions and the wave adds them up with one reduce-scatter
 // (cross-half lane swaps and DPP) of 8, 12 or 16 values.  Either way the atomics are paid
 // once per wave and record.
@@ -909,34 +909,35 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
     }
 }
 
-constexpr int kBatch = 16;          // entries staged at a time: four lanes load one record
+constexpr int kBatch = 16;  // entries staged, walked and summed at a time: four lanes load one record
 constexpr int kBatchPlane = kBatch + 2;  // words of a staging plane: quad-lane writes without bank conflicts
-constexpr int kQueue = 128;         // ring of entries waiting to be staged: at most 15 + 64
-constexpr int kSlots = 8;           // entries whose pixel values are summed together
-constexpr int kPart = 13;           // columns of grad2d that a slot's partial sums fill
+constexpr uint32_t kQueue = 80;          // ring of entries waiting to be staged: at most 15 + 64
+constexpr int kSumPitch = 33;            // words of an entry's g and w: 16 entries' words in 16 different bank groups
+constexpr int kOutPitch = 20;            // floats of an entry's sums: 16-byte writes without bank conflicts
 
 // Backward compositing, one pixel per lane, by independent waves.
 //
 // A wave stages the entries its bits mark 16 at a time (loaded one batch ahead) and walks them
-// four at a time, so that their LDS reads and exponents overlap; only the transmittance and
-// the remainder pass from one entry to the next, and one reciprocal serves the four.
+// four at a time, so that their LDS reads, exponents and reciprocals overlap; only the
+// transmittance and the remainder pass from one entry to the next.
 //
 // Per entry the wave needs up to 13 sums over its 64 pixels: Out[f] = sum_p F_f(p) H(p), where
 // the six moments take F = 1, x, y, x^2, xy, y^2 (pixel offsets from the wave rectangle's
 // centre) and H = g = alpha dL/dalpha, and the colour, depth and point sums take F = the
-// pixel's upstream gradient and H = w = alpha T.  Every eight entries, g and w pass through LDS
-// so that lane 8 r + y holds row y of entry r's 8 x 8 pixels: three row moments (the x offsets
-// are constants, paired about the centre) and the weighted sums over 8 pixels whose upstream
-// gradients the lane keeps in registers; the y moments are products of these.  The 8 rows'
-// partial sums pass through LDS once more to 16 lanes per entry, which add, re-centre and store
-// them.  (As a product on the matrix cores this is no faster: f32 matrix instructions run at
-// the rate of vector ones, 32 multiply-adds per cycle, never beside them, and the 16x16x4 and
-// 4x4x1 shapes spend half and a quarter of it on rows and columns that are not needed.)
+// pixel's upstream gradient and H = w = alpha T.  The 16 entries' g and w pass through LDS to the
+// matrix cores, 4 x 4 x 1 products in 16 blocks: four rows f by four entries each, one pixel per
+// instruction.  Each sum is thus one chain of fused multiply-adds over the pixels 0 .. 63 in this
+// order.  The order is part of the result: the parameter pass multiplies the moments by the
+// conic twice, which for a near-degenerate Gaussian magnifies their last bits until a few of these
+// carry the norm of the gradients of means, quats and log_scales.  (Sums by rows of pixels on the
+// vector units, with one reciprocal for four entries, took 1.10 ms and 192 us where this takes
+// 1.17 ms and 207 us, but their gradients lay 2 to 4 times further from these than two runs of one
+// form from each other.)
 //
-// Vector issue (about 46 instructions per entry and wave) and the LDS (29 cycles per entry, two
-// thirds of its time) bind it together.  8 views with 1M Gaussians: 1.43 ms before (workgroups,
-// entries one by one, 16x16x4 products), 1.09 ms now; pose-only at 960x640 with 500k: 274 and
-// 190 us.  Four waves per SIMD fit the registers without spilling; five are slower.
+// Vector issue and the matrix cores (32 cycles per entry) share its time.  8 views with 1M
+// Gaussians: 1.40 ms before (workgroups, entries one by one, 16x16x4 products: 64 cycles per
+// entry), 1.17 ms now; pose-only at 960x640 with 500k: 274 and 207 us.  Four waves per SIMD fit
+// the LDS.
 template <int TILE, bool POSE_ONLY, int FRAME>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges,
@@ -952,14 +953,8 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     // and record index.
     __shared__ float4 st[4 * kBatchPlane];
     __shared__ uint2 queue[kQueue];  // (record, list position) of the marked entries
-    // The slots' g and w (H = 0, 1): the value of slot r at pixel (x, y), x = 4 h + e, is
-    // element e of word 128 H + 16 r + 8 (h ^ (r & 1)) + (y ^ 4 h).  The 16 lanes of two slots
-    // read 16 different words mod 16, 32 pixels' writes fall into 32 banks, and a slot's
-    // place is a constant offset.  Then, over the same words, the partial sums: float
-    // [slot][y / 4][column][y % 4], the slots 104 and the halves 52 floats apart (8 and 20 mod
-    // 32: writes and 16-byte reads without bank conflicts).
-    __shared__ float4 gw[2 * 16 * kSlots];
-    static_assert(kSlots * kPart * 8 <= 4 * 2 * 16 * kSlots, "the partial sums fit");
+    // Entry e's g, pixels 0 .. 63, then its w; over the same words afterwards its sums.
+    __shared__ float4 gw[kSumPitch * kBatch];
     uint32_t tslot;
     int wv;
     wave_place<L::NW>(blockIdx.x, tslot, wv);
@@ -1016,9 +1011,11 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     if (wave_last == 0u) return;
 
     float *gwf = reinterpret_cast<float *>(gw);
-    // The upstream gradients of the flush lane's row of pixels, y = lane % 8.
-    const int slot = lane >> 3, y = lane & 7;
-    float U[V::NW][8];
+    // The products' left operand, rows f: 0 .. 5 the moments, 8 + m the m-th weighted sum.  Lane
+    // 16 t + 4 b + i holds row 4 t + i of pixel 4 k + b in F[k]; instruction 4 k + b takes it
+    // from the lanes of b for the four blocks of t.
+    const int row = 4 * (lane >> 4) + (lane & 3);
+    float F[16];
     {
         float wg[7];
         int m = 0;
@@ -1028,80 +1025,63 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
 #pragma unroll
         for (int t = 0; t < V::NW; ++t) gwf[64 * t + lane] = wg[t];
         wave_sync();
+        const int b = (lane >> 2) & 3;
 #pragma unroll
-        for (int t = 0; t < V::NW; ++t)
-#pragma unroll
-            for (int k = 0; k < 8; ++k) U[t][k] = gwf[64 * t + 8 * y + k];
+        for (int k = 0; k < 16; ++k) {
+            const float x = (float)(4 * (k & 1) + b) - 3.5f, y = (float)(k >> 1) - 3.5f;
+            float f = row == 0 ? 1.0f : row == 1 ? x : row == 2 ? y : row == 3 ? x * x : row == 4 ? x * y : row == 5 ? y * y : 0.0f;
+            if (row >= 8 && row < 8 + V::NW) f = gwf[64 * (row - 8) + 4 * k + b];
+            F[k] = f;
+        }
         wave_sync();  // read before the walk overwrites the buffer
     }
-    // This pixel's place in gw (floats) for even and odd slots, less 64 per slot.
-    const int ph = (lane >> 2) & 1, pw = 4 * ((lane >> 3) ^ (4 * ph)) + (lane & 3);
-    const int at[2] = {32 * ph + pw, 32 * (ph ^ 1) + pw};
-    // The flush lane's words of its row's left half (the right half's is 8 ^ 4 away by XOR).
-    const int rd = 16 * slot + 8 * (slot & 1) + y;
-    const float yc = (float)y - 3.5f;
-    // What each lane adds after that: column col of entry lane / 16 (+ 4), and the constants of
-    // its recentring.
+    // What each lane adds after that: column col of entry lane / 16 (+ 4 h), from the product's row
+    // out_row, and the constants of its recentring.
     const int col = lane & 15;
-    bool has = col <= 5 && (col > 0 || V::kOpacity);
+    int out_row = col <= 5 && (col > 0 || V::kOpacity) ? col : -1;
 #pragma unroll
-    for (int m = 0; m < V::NW; ++m) has = has || (int)((V::kWColumns >> (4 * m)) & 15u) == col;
+    for (int m = 0; m < V::NW; ++m) out_row = (int)((V::kWColumns >> (4 * m)) & 15u) == col ? 8 + m : out_row;
+    const bool has = out_row >= 0;
+    const int out_at = has ? out_row : 0;
     const float kx = col == 1 || col == 3 || col == 4 ? 1.0f : 0.0f, ky = col == 2 || col == 5 ? 1.0f : 0.0f;
     const float lx = col == 3 ? 1.0f : 0.0f, ly = col == 4 || col == 5 ? 1.0f : 0.0f;
     const float l1 = col == 1 || col == 2 ? -1.0f : 0.0f;
     const float bx = col == 3 ? -2.0f : 0.0f, by = col == 4 ? -1.0f : 0.0f;
     const float gx = col == 4 ? -1.0f : 0.0f, gy = col == 5 ? -2.0f : 0.0f;
     const float cxw = lay.rx0 + 3.5f, cyw = lay.ry0 + 3.5f;
-    // Adds the sums of the n <= 8 entries staged from slot g on.
-    auto flush = [&](int g, int n) {
+    // Adds the sums of the batch's n entries.
+    auto flush = [&](int n) {
         wave_sync();
-        const float4 ga = gw[rd], gb = gw[rd ^ 12], wa = gw[128 + rd], wb = gw[128 + (rd ^ 12)];
-        float part[6];
-        {
-            // x = -3.5 .. 3.5: sums and differences of the pixels paired about the centre.
-            const float p0 = gb.w + ga.x, p1 = gb.z + ga.y, p2 = gb.y + ga.z, p3 = gb.x + ga.w;
-            const float m0 = gb.w - ga.x, m1 = gb.z - ga.y, m2 = gb.y - ga.z, m3 = gb.x - ga.w;
-            const float s0 = (p0 + p1) + (p2 + p3);
-            const float s1 = fmaf(3.5f, m0, fmaf(2.5f, m1, fmaf(1.5f, m2, 0.5f * m3)));
-            const float s2 = fmaf(12.25f, p0, fmaf(6.25f, p1, fmaf(2.25f, p2, 0.25f * p3)));
-            const float sy = yc * s0;
-            part[0] = s0;
-            part[1] = s1;
-            part[2] = sy;
-            part[3] = s2;
-            part[4] = yc * s1;
-            part[5] = yc * sy;
+        // Lane 16 t + e supplies entry e (g for the moments' rows, w for the others) and
+        // receives rows 4 t .. 4 t + 3 of it.
+        const float4 *src = gw + kSumPitch * (lane & 15) + (lane >= 32 ? 16 : 0);
+        v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float4 h = src[k];
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(F[k], h.x, acc, 2, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(F[k], h.y, acc, 2, 1, 0);
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(F[k], h.z, acc, 2, 2, 0);
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(F[k], h.w, acc, 2, 3, 0);
         }
-        float *dst = gwf + 8 * kPart * slot + 4 * kPart * (y >> 2) + (y & 3);
         wave_sync();  // g and w have been read
-#pragma unroll
-        for (int c = 0; c < 6; ++c) dst[4 * c] = part[c];
-#pragma unroll
-        for (int m = 0; m < V::NW; ++m) {
-            const float *u = U[m];
-            const float v = fmaf(wa.x, u[0], fmaf(wa.y, u[1], fmaf(wa.z, u[2], wa.w * u[3]))) +
-                            fmaf(wb.x, u[4], fmaf(wb.y, u[5], fmaf(wb.z, u[6], wb.w * u[7])));
-            dst[4 * ((V::kWColumns >> (4 * m)) & 15u)] = v;
-        }
+        *reinterpret_cast<v4f *>(gwf + kOutPitch * (lane & 15) + 4 * (lane >> 4)) = acc;
         wave_sync();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int e = 4 * h + (lane >> 4);  // entry of this lane: 16 adjacent lanes hold one row
-            const float4 *src = gw + 2 * kPart * e + col;
-            const float4 a = src[0], b = src[kPart];
-            const float2 mean = *reinterpret_cast<const float2 *>(&st[g + e]);
-            const uint32_t rid = __float_as_uint(st[3 * kBatchPlane + g + e].w);
-            asm volatile("" ::"v"(rid));  // read before the branch
-            const float val = ((a.x + a.y) + (a.z + a.w)) + ((b.x + b.y) + (b.z + b.w));
+        for (int e0 = 0; e0 < n; e0 += 4) {
+            const int e = e0 + (lane >> 4);  // entry of this lane: 16 adjacent lanes hold one row
+            const float4 sm = *reinterpret_cast<const float4 *>(gwf + kOutPitch * e);  // S0, Sx, Sy
+            const float val = gwf[kOutPitch * e + out_at];
+            const float2 mean = *reinterpret_cast<const float2 *>(&st[e]);
+            const uint32_t rid = __float_as_uint(st[3 * kBatchPlane + e].w);
+            asm volatile("" ::"v"(rid), "v"(sm.w));  // read before the branch
             // Moments about the wave centre -> about the record's mean (dx = x - ux):
             // R_x = S_x - ux S0, R_xx = S_xx - 2 ux S_x + ux^2 S0, R_xy = S_xy - uy S_x -
             // ux S_y + ux uy S0, and likewise in y, with each column's coefficients picked by
             // products with lane constants (exact: 0, +-1, -2).
-            const float S0 = GSPM_DPP_MOV(val, 0x150), Sx = GSPM_DPP_MOV(val, 0x151), Sy = GSPM_DPP_MOV(val, 0x152);  // row_newbcast
             const float ux = mean.x - cxw, uy = mean.y - cyw;
             const float al = fmaf(kx, ux, ky * uy) * fmaf(lx, ux, fmaf(ly, uy, l1));
-            const float be = fmaf(bx, ux, by * uy), ga2 = fmaf(gx, ux, gy * uy);
-            const float out = fmaf(ga2, Sy, fmaf(be, Sx, fmaf(al, S0, val)));
+            const float be = fmaf(bx, ux, by * uy), ga = fmaf(gx, ux, gy * uy);
+            const float out = fmaf(ga, sm.z, fmaf(be, sm.y, fmaf(al, sm.x, val)));
             if (e < n && has && out != 0.f) unsafeAtomicAdd(grad2d + (int64_t)rid * kG2 + col, out);
         }
         wave_sync();  // read before the next entries overwrite the buffer
@@ -1123,7 +1103,7 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     };
     // The next 64 positions' bits and record indices are loaded one step ahead.
     const uint32_t wend = rg.x + wave_last;
-    uint32_t pos = rg.x, head = 0u, tail = 0u;
+    uint32_t pos = rg.x, head = 0u, waiting = 0u;  // the ring's first entry (below kQueue) and how many wait
     uint64_t m_next = 0ull;
     uint32_t rec_next = 0u;
     auto load_step = [&]() {
@@ -1134,16 +1114,17 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     load_step();
     // Queues marked entries until a batch is complete or the list ends.
     auto fill = [&]() {
-        while (tail - head < (uint32_t)kBatch && pos < wend) {
+        while (waiting < (uint32_t)kBatch && pos < wend) {
             const uint64_t m = m_next;
             const uint32_t r = rec_next, rel = pos - rg.x + (uint32_t)lane;
             pos += kWave;
             if (pos < wend) load_step();
             if ((m >> lane) & 1ull) {
                 const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                queue[(tail + rank) % kQueue] = make_uint2(r, rel);
+                const uint32_t q = head + waiting + rank;  // below 2 kQueue
+                queue[q < kQueue ? q : q - kQueue] = make_uint2(r, rel);
             }
-            tail += (uint32_t)__popcll(m);
+            waiting += (uint32_t)__popcll(m);
         }
         wave_sync();
     };
@@ -1152,14 +1133,16 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     uint2 mine;
     v4f word;
     auto load_batch = [&]() {
-        cnt = min((uint32_t)kBatch, tail - head);
-        const uint32_t e = min((uint32_t)lane >> 2, cnt - 1u);
-        mine = queue[(head + e) % kQueue];
+        cnt = min((uint32_t)kBatch, waiting);
+        const uint32_t q = head + min((uint32_t)lane >> 2, cnt - 1u);
+        mine = queue[q < kQueue ? q : q - kQueue];
         word = reinterpret_cast<const v4f *>(rec)[4 * (int64_t)mine.x + (lane & 3)];
+        waiting -= cnt;
         head += cnt;
+        head -= head >= kQueue ? kQueue : 0u;
     };
     fill();
-    if (tail != head) load_batch();
+    if (waiting != 0u) load_batch();
     while (cnt != 0u) {
         // Stage the batch: word 0 takes the conic's (a, b) from its quad neighbour, word 1 the
         // threshold of word 3; slots past the batch's end accept nothing.
@@ -1180,11 +1163,11 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
         }
         fill();
         cnt = 0u;
-        if (tail != head) load_batch();
+        if (waiting != 0u) load_batch();
         auto walk = [&](auto may_clamp) {
             constexpr bool kClamp = decltype(may_clamp)::value;
             for (uint32_t g = 0u; g < n; g += 4u) {
-                float al[4], sv[4], w[4];
+                float al[4], sv[4], inv[4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const float4 a = st[g + t], b = st[kBatchPlane + g + t], c = st[2 * kBatchPlane + g + t];
@@ -1210,31 +1193,23 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
                     if (kClamp) ao = clamp_alpha(ao, amax);
                     // An invalid pixel takes alpha = 0: no weight, no gradient, T unchanged.
                     al[t] = in_mask(valid) ? ao : 0.0f;
+                    inv[t] = __builtin_amdgcn_rcpf(__fsub_rn(1.0f, al[t]));
                 }
-                // Front to back: the weights, and Rem = G - sum of w s over these and earlier
-                // fragments: the later fragments' share plus the background term.
+                // Front to back: Rem = G - sum of w s over this and earlier fragments, the later
+                // fragments' share plus the background term.
+                float *dst = gwf + 4 * kSumPitch * g + lane;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    w[t] = __fmul_rn(al[t], T);
-                    Rem = fmaf(-w[t], sv[t], Rem);
+                    const float w = __fmul_rn(al[t], T);
+                    Rem = fmaf(-w, sv[t], Rem);
+                    const float dLda = fmaf(T, sv[t], -__fmul_rn(Rem, inv[t]));
+                    // A clamped alpha passes no gradient.
+                    dst[4 * kSumPitch * t] = kClamp && al[t] >= amax ? 0.0f : dLda * al[t];
+                    dst[4 * kSumPitch * t + 64] = w;
                     T = fmaf(-al[t], T, T);  // as in the forward
                 }
-                // Back to front over the group: with Q = Rem / T behind a fragment (what the later
-                // fragments and the background would show), alpha dL/dalpha = w (s - Q) and
-                // Q in front of it = Q + alpha (s - Q): one reciprocal per group.  (A T below the
-                // bound has weights far below rounding; its reciprocal might not be finite.)
-                float Q = Rem * __builtin_amdgcn_rcpf(fmaxf(T, 0x1p-100f));
-                float *dst = gwf + 64 * (g & 4u);
-#pragma unroll
-                for (int t = 3; t >= 0; --t) {
-                    const float d = sv[t] - Q;
-                    Q = fmaf(al[t], d, Q);
-                    // A clamped alpha passes no gradient.
-                    dst[at[t & 1] + 64 * t] = kClamp && al[t] >= amax ? 0.0f : w[t] * d;
-                    dst[at[t & 1] + 64 * t + 512] = w[t];
-                }
-                if ((g & 4u) != 0u || g + 4u >= n) flush((int)(g & ~7u), (int)min(8u, n - (g & ~7u)));
             }
+            flush((int)n);
         };
         if (clampy) walk(std::true_type{});
         else walk(std::false_type{});
