@@ -459,8 +459,11 @@ k_raster_fwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     float py = inside ? (float)lay.ly : __uint_as_float(kNan);
     // A bound on the list entries that the backward considers: an entry before it contributes
     // to the pixel exactly when its alpha reaches alpha_min.  A stopped pixel's is the entry
-    // that stopped it; otherwise the end of the last chunk in which it composited.
+    // that stopped it; otherwise the end of the last chunk in which it composited, which
+    // shows in T, unless the settings admit an alpha that T (1 - alpha) rounds away: then the
+    // end of the last chunk that it met.
     uint32_t n_last = 0u;
+    const bool faint = !(rs.alpha_min >= 0x1p-23f && tmin >= 0x1p-100f);
     uint64_t live = ballot(py == py);  // lanes that still composite, re-evaluated once per chunk
     // The rectangle of the wave's live pixels, which the chunks are culled against: once
     // pixels stop, the entries that only they would take are not walked.  Scalar bit work on
@@ -611,7 +614,7 @@ k_raster_fwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
             atomicOr((unsigned long long *)w, (unsigned long long)(composited << sh));
             if (sh != 0) atomicOr((unsigned long long *)(w + 1), (unsigned long long)(composited >> (64 - sh)));
         }
-        n_last = T != T0 ? min(c0 + (uint32_t)kChunk, n) : n_last;
+        n_last = T != T0 || (faint && py == py) ? min(c0 + (uint32_t)kChunk, n) : n_last;
         const uint64_t now = ballot(py == py);
         if (now != live) {  // wave-uniform: some pixels stopped in this chunk
             const uint32_t pb = __float_as_uint(py);
