@@ -39,7 +39,8 @@ struct RasterSettings {
 // Projected record of one (Gaussian, view) pair: 64 bytes, 4 x float4.
 //   r0 = (u_hi, v_hi, u_lo, v_lo)     mean2D as a float32 pair (u = u_hi + u_lo)
 //   r1 = (a, b, c, opacity)           factored conic, base 2:
-//                                     alpha = opacity * 2^-((a dx + b dy)^2 + (c dy)^2)
+//                                     alpha = opacity * 2^-((a dx + b dy)^2 + (c dy)^2);
+//                                     c < 0 where r2 or the point is not finite, else c > 0
 //   r2 = (c_r, c_g, c_b, z)           colour and camera depth
 //   r3 = (p_x, p_y, p_z, t)           composited point (world centre or camera centre) and
 //                                     the acceptance threshold t = -log2(alpha_min / opacity)

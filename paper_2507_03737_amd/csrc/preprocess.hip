@@ -157,16 +157,20 @@ k_preprocess(gspm_gaussians G, ViewTable vt, const float *__restrict__ T_cw, Ras
                 const double fa = sqrt(kq * P.Q[0]);
                 const double fb = kq * P.Q[1] / fa;
                 const double fc = sqrt(kq * (P.Q[0] * P.Q[2] - P.Q[1] * P.Q[1]) / P.Q[0]);
-                const float4 r1 = make_float4((float)fa, (float)fb, (float)fc, (float)P.a);
+                float4 r1 = make_float4((float)fa, (float)fb, (float)fc, (float)P.a);
+                const float4 r2 = make_float4(G.rgb[g], G.rgb[n + g], G.rgb[2 * n + g], zf);
+                const float thr = accept_threshold(rs.alpha_min, r1.w);
+                const float4 r3 = rs.frame == 0 ? make_float4(G.means[g], G.means[n + g], G.means[2 * n + g], thr)
+                                                : make_float4((float)P.m[0], (float)P.m[1], (float)P.m[2], thr);
+                // c's sign is free: it marks a value that is not finite (0 x it is NaN).
+                const float odd = ((r2.x * 0.0f + r2.y * 0.0f) + (r2.z * 0.0f + r2.w * 0.0f)) +
+                                  ((r3.x * 0.0f + r3.y * 0.0f) + r3.z * 0.0f);
+                r1.z = odd == 0.0f ? r1.z : -r1.z;
                 float4 *o = rec + 4 * r;
                 o[0] = r0;
                 o[1] = r1;
-                o[2] = make_float4(G.rgb[g], G.rgb[n + g], G.rgb[2 * n + g], zf);
-                const float thr = accept_threshold(rs.alpha_min, r1.w);
-                if (rs.frame == 0)
-                    o[3] = make_float4(G.means[g], G.means[n + g], G.means[2 * n + g], thr);
-                else
-                    o[3] = make_float4((float)P.m[0], (float)P.m[1], (float)P.m[2], thr);
+                o[2] = r2;
+                o[3] = r3;
                 // Number of tiles the support meets, row by row (the pair emission repeats this).
                 // Records whose support box covers many tiles are counted by whole waves instead.
                 Footprint f;

@@ -545,17 +545,19 @@ k_raster_fwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
             return quad_s(a.z * dx, a.w, b.x, py - a.y);
         };
         // One entry's share of the wave's pixels, which may stop some of them (ok: the lanes
-        // that accept it; stopped lanes leave ok_next, the next entry's).  may_clamp: some
-        // opacity of the chunk reaches alpha_max (otherwise o exp2(-s) <= o < alpha_max and the
-        // clamp is the identity).
-        auto composite = [&](auto may_clamp, int q, const float4 &b, const float4 &cc, const float4 &d, float sq,
+        // that accept it; stopped lanes leave ok_next, the next entry's).  special: some opacity
+        // of the chunk reaches alpha_max (otherwise o exp2(-s) <= o < alpha_max and the clamp is
+        // the identity), or some colour or point is not finite: then an entry that no pixel
+        // accepts is left out (its weight 0 times infinity would be NaN; otherwise it adds 0).
+        auto composite = [&](auto special, int q, const float4 &b, const float4 &cc, const float4 &d, float sq,
                              uint64_t ok, uint64_t &ok_next) {
             // Some live pixel accepts the entry: it is composited there or stops that pixel.
             // The backward walks these entries (a superset of those it finds a valid pixel for;
             // it skips the rest), scalar work only.
+            if (decltype(special)::value && ok == 0ull) return;  // wave-uniform
             composited |= ok != 0ull ? 1ull << q : 0ull;
             float al = b.z * __builtin_amdgcn_exp2f(-sq);
-            if (decltype(may_clamp)::value) al = clamp_alpha(al, amax);
+            if (decltype(special)::value) al = clamp_alpha(al, amax);
             const float Tn = fmaf(-al, T, T);  // T (1 - alpha), rounded once
             // One comparison; the lane masks combine in scalar code.
             const uint64_t over = ballot(!(Tn < tmin));
@@ -575,7 +577,7 @@ k_raster_fwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
             T = in_mask(add) ? Tn : T;
             py = in_mask(stop) ? b.w : py;  // NaN with the entry's slot
         };
-        auto walk_pairs = [&](auto may_clamp) {
+        auto walk_pairs = [&](auto special) {
             for (int p = (int)__popcll(m) >> 1; p > 0; --p) {
                 const int q0 = (int)__builtin_ctzll(m);
                 m ^= 1ull << q0;
@@ -587,11 +589,11 @@ k_raster_fwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
                 asm volatile("" ::"v"(b0.w), "v"(b1.w));
                 const float s0 = exponent(a0, b0), s1 = exponent(a1, b1);
                 uint64_t ok0 = ballot(s0 <= b0.y), ok1 = ballot(s1 <= b1.y), none = 0ull;
-                composite(may_clamp, q0, b0, e0, d0, s0, ok0, ok1);
-                composite(may_clamp, q1, b1, e1, d1, s1, ok1, none);
+                composite(special, q0, b0, e0, d0, s0, ok0, ok1);
+                composite(special, q1, b1, e1, d1, s1, ok1, none);
             }
         };
-        if ((ballot(sb.z >= amax) & m) != 0ull) walk_pairs(std::true_type{});
+        if ((ballot(sb.z >= amax || sb.x < 0.0f) & m) != 0ull) walk_pairs(std::true_type{});
         else walk_pairs(std::false_type{});
         if (m != 0ull) {  // the last of an odd number
             const int q = (int)__builtin_ctzll(m);
@@ -1052,8 +1054,8 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     const float bx = col == 3 ? -2.0f : 0.0f, by = col == 4 ? -1.0f : 0.0f;
     const float gx = col == 4 ? -1.0f : 0.0f, gy = col == 5 ? -2.0f : 0.0f;
     const float cxw = lay.rx0 + 3.5f, cyw = lay.ry0 + 3.5f;
-    // Adds the sums of the batch's n entries.
-    auto flush = [&](int n) {
+    // Adds the sums of those of the batch's n entries that adds marks.
+    auto flush = [&](uint32_t n, uint32_t adds) {
         wave_sync();
         // Lane 16 t + e supplies entry e (g for the moments' rows, w for the others) and
         // receives rows 4 t .. 4 t + 3 of it.
@@ -1070,8 +1072,8 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
         wave_sync();  // g and w have been read
         *reinterpret_cast<v4f *>(gwf + kOutPitch * (lane & 15) + 4 * (lane >> 4)) = acc;
         wave_sync();
-        for (int e0 = 0; e0 < n; e0 += 4) {
-            const int e = e0 + (lane >> 4);  // entry of this lane: 16 adjacent lanes hold one row
+        for (uint32_t e0 = 0u; e0 < n; e0 += 4u) {
+            const uint32_t e = e0 + ((uint32_t)lane >> 4);  // entry of this lane: 16 adjacent lanes hold one row
             const float4 sm = *reinterpret_cast<const float4 *>(gwf + kOutPitch * e);  // S0, Sx, Sy
             const float val = gwf[kOutPitch * e + out_at];
             const float2 mean = *reinterpret_cast<const float2 *>(&st[e]);
@@ -1085,7 +1087,7 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
             const float al = fmaf(kx, ux, ky * uy) * fmaf(lx, ux, fmaf(ly, uy, l1));
             const float be = fmaf(bx, ux, by * uy), ga = fmaf(gx, ux, gy * uy);
             const float out = fmaf(ga, sm.z, fmaf(be, sm.y, fmaf(al, sm.x, val)));
-            if (e < n && has && out != 0.f) unsafeAtomicAdd(grad2d + (int64_t)rid * kG2 + col, out);
+            if (((adds >> e) & 1u) != 0u && has && out != 0.f) unsafeAtomicAdd(grad2d + (int64_t)rid * kG2 + col, out);
         }
         wave_sync();  // read before the next entries overwrite the buffer
     };
@@ -1144,13 +1146,16 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
         head += cnt;
         head -= head >= kQueue ? kQueue : 0u;
     };
+    // Whether some upstream gradient, image, colour or point is not finite: 0 times it is NaN, so an
+    // entry without a valid pixel is left out (otherwise it adds 0).
+    bool odd = ballot(!(fabsf(Rem) < __builtin_inff())) != 0ull;
     fill();
     if (waiting != 0u) load_batch();
     while (cnt != 0u) {
         // Stage the batch: word 0 takes the conic's (a, b) from its quad neighbour, word 1 the
         // threshold of word 3; slots past the batch's end accept nothing.
         const uint32_t n = cnt;
-        bool clampy;
+        bool special;
         {
             const int w = lane & 3;
             const bool dead = (uint32_t)lane >> 2 >= n;
@@ -1160,15 +1165,17 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
             if (w == 0) o = make_float4((word.x - tp.x0) + word.z, (word.y - tp.y0) + word.w, ca, cb);
             if (w == 1) o = make_float4(word.z, dead ? -__builtin_inff() : thr, word.w, __uint_as_float(mine.y));
             if (w == 3) o.w = __uint_as_float(mine.x);
-            clampy = ballot(w == 1 && word.w >= amax) != 0ull;
+            odd = odd || ballot(w == 1 && word.z < 0.0f) != 0ull;
+            special = odd || ballot(w == 1 && word.w >= amax) != 0ull;
             wave_sync();  // the previous batch has been read
             st[w * kBatchPlane + (lane >> 2)] = o;
         }
         fill();
         cnt = 0u;
         if (waiting != 0u) load_batch();
-        auto walk = [&](auto may_clamp) {
-            constexpr bool kClamp = decltype(may_clamp)::value;
+        auto walk = [&](auto special) {
+            constexpr bool kClamp = decltype(special)::value, kSkip = kClamp;
+            uint32_t adds = kSkip ? 0u : (1u << n) - 1u;  // the batch's entries that add anything
             for (uint32_t g = 0u; g < n; g += 4u) {
                 float al[4], sv[4], inv[4];
 #pragma unroll
@@ -1196,6 +1203,10 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
                     if (kClamp) ao = clamp_alpha(ao, amax);
                     // An invalid pixel takes alpha = 0: no weight, no gradient, T unchanged.
                     al[t] = in_mask(valid) ? ao : 0.0f;
+                    if (kSkip) {
+                        sv[t] = valid != 0ull ? sv[t] : 0.0f;
+                        adds |= (valid != 0ull ? 1u : 0u) << (g + t);
+                    }
                     inv[t] = __builtin_amdgcn_rcpf(__fsub_rn(1.0f, al[t]));
                 }
                 // Front to back: Rem = G - sum of w s over this and earlier fragments, the later
@@ -1212,9 +1223,9 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
                     T = fmaf(-al[t], T, T);  // as in the forward
                 }
             }
-            flush((int)n);
+            flush(n, adds);
         };
-        if (clampy) walk(std::true_type{});
+        if (special) walk(std::true_type{});
         else walk(std::false_type{});
     }
 }
