@@ -157,7 +157,8 @@ GSPM_API void gspm_destroy(gspm_ctx *ctx);
 
 /* Grow the context's scratch so that later calls with at most max_records
  * Gaussian-view records (n * n_views), max_pairs tile pairs and max_tiles tiles
- * allocate nothing.  Sizes never shrink.  Both counts must be below 2^30 (the radix
+ * allocate nothing.  (The window loss, the scale alignment and the pose initialisation
+ * size theirs by patches, hypotheses and matches: on their first call.)  Sizes never shrink.  Both counts must be below 2^30 (the radix
  * sorts' limit; GSPM_ERR_INVALID_ARG otherwise). */
 GSPM_API gspm_status gspm_reserve(gspm_ctx *ctx, int64_t max_records, int64_t max_pairs, int64_t max_tiles);
 

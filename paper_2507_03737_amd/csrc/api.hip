@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -223,6 +224,13 @@ hipError_t ensure_records(gspm_ctx *c, int64_t R, int digit_bits) {
     return hipSuccess;
 }
 
+// Scratch that the regulariser, covisibility and median calls share: of one size from the first use
+// on, so that none of them moves what another one's captured graph writes to.
+hipError_t ensure_aux(gspm_ctx *c) {
+    return grow(c->aux, std::max(std::max<int64_t>(8 * iso_partials(), 8 * (int64_t)kMaxViews * kMaxViews),
+                                 4 * median_scratch_words(kMaxViews)));
+}
+
 hipError_t ensure_pairs(gspm_ctx *c, int64_t cap, int digit_bits) {
     const int64_t w = cap > 0 ? cap : 1;
     hipError_t e;
@@ -317,9 +325,12 @@ gspm_status gspm_reserve(gspm_ctx *ctx, int64_t max_records, int64_t max_pairs, 
     if (max_records < 0 || max_pairs < 0 || max_tiles < 0) return fail(GSPM_ERR_INVALID_ARG, "negative size");
     if (max_pairs >= kMaxSortKeys || max_records >= kMaxSortKeys)
         return fail(GSPM_ERR_INVALID_ARG, "sizes must be < 2^30");
-    (void)max_tiles;
     GSPM_HIP(ensure_records(ctx, max_records, 8));
     GSPM_HIP(ensure_pairs(ctx, max_pairs, 8));
+    GSPM_HIP(ensure_aux(ctx));
+    GSPM_HIP(grow(ctx->twork, 4 * max_tiles));
+    // The partials of n Gaussians in V views: most for many views of few.
+    GSPM_HIP(grow(ctx->pose_part, 8 * 6 * (pose_partial_blocks(max_records) + pose_partial_blocks(1) * kMaxViews)));
     const void *g2_before = ctx->grad2d.p;
     GSPM_HIP(grow(ctx->grad2d, 4 * kG2 * (max_records > 0 ? max_records : 1)));
     if (ctx->grad2d.p != g2_before) ctx->grad2d_clean = false;
@@ -649,7 +660,7 @@ gspm_status gspm_iso_loss(gspm_ctx *ctx, const gspm_gaussians *g, float weight, 
     if (!g || g->n < 0 || (g->n > 0 && !g->log_scales)) return fail(GSPM_ERR_INVALID_ARG, "Gaussians are invalid");
     if (!loss_out) return fail(GSPM_ERR_INVALID_ARG, "loss_out is required");
     if (!std::isfinite(weight)) return fail(GSPM_ERR_INVALID_ARG, "weight must be finite");
-    GSPM_HIP(grow(ctx->aux, 8 * iso_partials()));
+    GSPM_HIP(ensure_aux(ctx));
     GSPM_HIP(launch_iso_loss(g->log_scales, g->n, weight, static_cast<double *>(ctx->aux.p), loss_out,
                              grad_log_scales, reinterpret_cast<hipStream_t>(stream)));
     return GSPM_OK;
@@ -666,7 +677,7 @@ gspm_status gspm_covisibility(gspm_ctx *ctx, const gspm_views *views, int64_t n_
     if (st) return st;
     const FrameLayout L = frame_layout(0, 0, n_gaussians * vt.n_views, 0);
     const int V = vt.n_views;
-    GSPM_HIP(grow(ctx->aux, 8 * (int64_t)V * V));
+    GSPM_HIP(ensure_aux(ctx));
     GSPM_HIP(launch_covisibility(at<uint8_t>(frame_state, L.visible), n_gaussians, V,
                                  at<FrameHeader>(frame_state, L.header),
                                  static_cast<unsigned long long *>(ctx->aux.p), iou_out, oc_out, count_out,
@@ -682,7 +693,7 @@ gspm_status gspm_median_depth(gspm_ctx *ctx, const gspm_views *views, const floa
     int64_t nt, np;
     gspm_status st = build_views(views, 16, vt, nt, np);
     if (st) return st;
-    GSPM_HIP(grow(ctx->aux, 4 * median_scratch_words(vt.n_views)));
+    GSPM_HIP(ensure_aux(ctx));
     GSPM_HIP(launch_median_depth(vt, depth, static_cast<uint32_t *>(ctx->aux.p), median_out,
                                  reinterpret_cast<hipStream_t>(stream)));
     return GSPM_OK;
