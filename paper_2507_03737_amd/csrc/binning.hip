@@ -937,6 +937,7 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
         hdr->counted = (uint32_t)rs.count_work;
         hdr->ppt = (uint32_t)vt.ppt;
         hdr->frame = (uint32_t)rs.frame;
+        hdr->alpha_min = rs.alpha_min;
         hdr->bwd_error = 0u;
         hdr->walked = hdr->accepted = 0u;
     }

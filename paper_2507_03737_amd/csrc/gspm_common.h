@@ -113,7 +113,7 @@ struct FrameHeader {
     uint32_t ppt;         // pixels per lane of the forward, whose waves the contribution bits follow
     uint32_t frame;       // pointmap frame of the forward (the records carry that frame's point)
     uint32_t bwd_error;   // set by a backward that found the frame state unusable (see k_raster_bwd)
-    uint32_t pad;
+    float alpha_min;      // of the forward, whose records' acceptance thresholds follow it
     uint64_t walked;      // counting forward: (wave, list entry) pairs its waves walked
     uint64_t accepted;    // counting forward: of those, the ones a live pixel of the wave accepted
 };

@@ -76,22 +76,20 @@ __device__ inline TilePos tile_pos(const ViewTable &vt, const uint32_t *order, u
 // Stage record r into LDS slot q, in tile-local pixel coordinates, with the record's
 // threshold -e_min (see accept_threshold): alpha >= alpha_min exactly when the base-2
 // exponent e = -s >= e_min, i.e. s <= -e_min, so rejected pixels never evaluate the
-// exponential.
+// exponential.  own_min > 0: with the threshold for this alpha_min instead.
 //   s0 = (u, v, a, b), s1 = (c, -e_min, opacity, record index), s2 = (colour, z), s3 = point
 // with (a, b, c) the factored conic of the record.
 // The acceptance test reads s0 and s1 only.
-// With a list position pos, it replaces the point's unused fourth component (one 16-byte
-// write instead of that write and a 4-byte one at a 16-byte stride, a 4-way conflict).
 __device__ inline void stage(const float4 *__restrict__ rec, uint32_t r, float x0, float y0, float4 *s0, float4 *s1,
-                             float4 *s2, float4 *s3, int q, const uint32_t *pos = nullptr) {
+                             float4 *s2, float4 *s3, int q, float own_min = 0.0f) {
     const float4 *src = rec + 4 * (int64_t)r;
     const float4 a = src[0], b = src[1], c = src[2], d = src[3];
     const float ul = (a.x - x0) + a.z;
     const float vl = (a.y - y0) + a.w;
     s0[q] = make_float4(ul, vl, b.x, b.y);
-    s1[q] = make_float4(b.z, d.w, b.w, __uint_as_float(r));
+    s1[q] = make_float4(b.z, own_min > 0.0f ? accept_threshold(own_min, b.w) : d.w, b.w, __uint_as_float(r));
     s2[q] = c;
-    s3[q] = pos ? make_float4(d.x, d.y, d.z, __uint_as_float(*pos)) : d;
+    s3[q] = d;
 }
 
 // min(alpha_max, a) for a >= 0, as one median instruction (min would first quiet a
@@ -684,6 +682,11 @@ struct BwdValues {
     static constexpr uint32_t kWColumns = (uint32_t)(kColumns >> (4 * (N - NW)));
 };
 
+// A backward with another alpha_min than its forward's: its own, for its own thresholds; else 0.
+__device__ inline float own_alpha_min(const RasterSettings &rs, const FrameHeader *hdr) {
+    return hdr->alpha_min == rs.alpha_min ? 0.0f : rs.alpha_min;
+}
+
 // The frame state's layout follows the views, Gaussian count and tile of the call: unless they
 // (and the pointmap frame of the records) are the forward's, and the forward's lists are
 // complete, a backward may read nothing of it.  The test is uniform over the launch; one lane
@@ -716,7 +719,7 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
     const L lay;
     const int lx = lay.lx, ly = lay.ly;
     const float px = (float)lx;
-    const float amax = rs.alpha_max;
+    const float amax = rs.alpha_max, own_min = own_alpha_min(rs, hdr);
     const int i = tp.tx * TILE + lx;
     // Per-pixel upstream gradient and, to start the walk's remainder Rem, the total
     // G = sum_k w_k (g . e_k) + T_final (g_C . bg) that the forward's outputs give.
@@ -882,7 +885,7 @@ k_raster_bwd(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges, 
         const uint32_t vcur = vnext;
         if (kk + NT < end) vnext = vals[kk + NT];
         const uint64_t bits0 = use_bits ? wave_bits(base) : 0ull;  // read while the batch is staged
-        if (kk < end) stage(rec, vcur, tp.x0, tp.y0, s0, s1, s2, s3, threadIdx.x);
+        if (kk < end) stage(rec, vcur, tp.x0, tp.y0, s0, s1, s2, s3, threadIdx.x, own_min);
         __syncthreads();
         const int cnt = (int)min((uint32_t)NT, end - base);
         const uint32_t rel0 = base - rg.x;
@@ -968,7 +971,7 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
     const uint2 rg = ranges[tp.gt];
     const L lay(wv);
     const int lane = lane_id();
-    const float px = (float)lay.lx, py = (float)lay.ly, amax = rs.alpha_max;
+    const float px = (float)lay.lx, py = (float)lay.ly, amax = rs.alpha_max, own_min = own_alpha_min(rs, hdr);
     const int i = tp.tx * TILE + lay.lx, j = tp.ty * TILE + lay.ly;
     // The pixel's upstream gradient and, to start the walk's remainder Rem, the total
     // G = sum_k w_k (g . e_k) + T_final (g_C . bg) that the forward's outputs give.
@@ -1161,7 +1164,8 @@ k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ra
             const bool dead = (uint32_t)lane >> 2 >= n;
             float4 o = make_float4(word.x, word.y, word.z, word.w);
             const float ca = GSPM_DPP_MOV(o.x, 0x55), cb = GSPM_DPP_MOV(o.y, 0x55);  // lane 1 of the quad
-            const float thr = GSPM_DPP_MOV(o.w, 0xff);                               // lane 3
+            float thr = GSPM_DPP_MOV(o.w, 0xff);                                     // lane 3
+            if (own_min > 0.0f) thr = accept_threshold(own_min, word.w);             // used by lane 1
             if (w == 0) o = make_float4((word.x - tp.x0) + word.z, (word.y - tp.y0) + word.w, ca, cb);
             if (w == 1) o = make_float4(word.z, dead ? -__builtin_inff() : thr, word.w, __uint_as_float(mine.y));
             if (w == 3) o.w = __uint_as_float(mine.x);
