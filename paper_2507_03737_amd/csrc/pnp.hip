@@ -18,6 +18,7 @@
 //   k_pnp_finish  the last update, inlier mask and count of the final pose, and the results.
 // Everything is float64; the inputs are float32.
 #include <algorithm>
+#include <type_traits>
 
 #include "gspm_common.h"
 
@@ -324,27 +325,34 @@ __device__ inline bool inlier(const Pose &P, double x, double y, double z, doubl
 // Float64 arithmetic binds this (about 30 instructions per match and hypothesis); a workgroup
 // takes two hypotheses, so that the loads and conversions of a match serve both, and a point's
 // one reciprocal serves both coordinates: 20000 matches, 1024 hypotheses: 54 us with one
-// hypothesis per workgroup and two divisions, 38 us now (four hypotheses: 43 us).
+// hypothesis per workgroup and two divisions, 38 us now (four hypotheses: 43 us).  Invalid
+// hypotheses are not counted.
 __global__ void __launch_bounds__(kScoreBlock)
 k_pnp_score(const float *__restrict__ X, const float *__restrict__ uv, int64_t n, gspm_intrinsics K, double thr2,
             const Pose *__restrict__ poses, const int32_t *__restrict__ valid, int H, int32_t *__restrict__ scores,
             PnpState *__restrict__ st) {
     __shared__ int lds[kScoreHyps][kScoreBlock / kWave];
     const int h0 = blockIdx.x * kScoreHyps;
-    Pose P[kScoreHyps];
-    int cnt[kScoreHyps];
-#pragma unroll
-    for (int i = 0; i < kScoreHyps; ++i) {
-        P[i] = poses[min(h0 + i, H - 1)];
-        cnt[i] = 0;
-    }
-    for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
-        const double x = X[k], y = X[n + k], z = X[2 * n + k], u0 = uv[k], v0 = uv[n + k];
-#pragma unroll
-        for (int i = 0; i < kScoreHyps; ++i) {
+    static_assert(kScoreHyps == 2, "both, one or none");
+    int cnt[kScoreHyps] = {0, 0};
+    const bool first = valid[h0] != 0, second = h0 + 1 < H && valid[h0 + 1] != 0;
+    auto count = [&](auto both, const Pose &P0, const Pose &P1, int &c0, int &c1) {
+        for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
+            const double x = X[k], y = X[n + k], z = X[2 * n + k], u0 = uv[k], v0 = uv[n + k];
             double r[2], Y[3];
-            cnt[i] += inlier(P[i], x, y, z, u0, v0, K, thr2, r, Y) ? 1 : 0;
+            c0 += inlier(P0, x, y, z, u0, v0, K, thr2, r, Y) ? 1 : 0;
+            if (decltype(both)::value) c1 += inlier(P1, x, y, z, u0, v0, K, thr2, r, Y) ? 1 : 0;
         }
+    };
+    if (first && second) {
+        const Pose P0 = poses[h0], P1 = poses[h0 + 1];
+        count(std::true_type{}, P0, P1, cnt[0], cnt[1]);
+    } else if (first || second) {
+        const Pose P0 = poses[first ? h0 : h0 + 1];
+        int c = 0;
+        count(std::false_type{}, P0, P0, c, c);
+        cnt[0] = first ? c : 0;
+        cnt[1] = first ? 0 : c;
     }
 #pragma unroll
     for (int i = 0; i < kScoreHyps; ++i) {
