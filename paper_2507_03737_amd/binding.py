@@ -18,6 +18,7 @@ LIB_PATH = os.path.join(_HERE, "libgspm.so")
 
 GSPM_OK, GSPM_ERR_INVALID_ARG, GSPM_ERR_CAPACITY, GSPM_ERR_HIP, GSPM_ERR_INTERNAL = 0, 1, 2, 3, 4
 MAX_VIEWS = 32
+MAX_PAIRS = (1 << 30) - 1  # most tile pairs of a frame state
 
 vp = ctypes.c_void_p
 fp = ctypes.POINTER(ctypes.c_float)

@@ -69,6 +69,34 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t x, uint32_t *lds, uint3
     return wave_base + inc - x;
 }
 
+// Sums of pair counts stop at 2^32 - 1: a window of 133k screen-filling records has more pairs (1920x1080
+// at 8 x 8 tiles), and a sum that wrapped would pass for one that fits the frame state.  Saturating
+// addition is associative, so the scans need no more than that.
+__device__ inline uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+
+// block_exclusive_scan with saturating sums.
+__device__ inline uint32_t block_exclusive_scan_sat(uint32_t x, uint32_t *lds, uint32_t &total) {
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    uint32_t inc = x;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d, kWave);
+        if (lane >= d) inc = add_sat(inc, y);
+    }
+    if (lane == kWave - 1) lds[wid] = inc;
+    __syncthreads();
+    uint32_t before = __shfl_up(inc, 1, kWave), tot = 0u;
+    if (lane == 0) before = 0u;
+    for (int k = 0; k < kScanBlock / kWave; ++k) {
+        const uint32_t t = lds[k];
+        if (k < wid) before = add_sat(before, t);
+        tot = add_sat(tot, t);
+    }
+    __syncthreads();
+    total = tot;
+    return before;
+}
+
 __global__ void __launch_bounds__(kScanBlock)
 k_scan_reduce(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ idx, const uint32_t *__restrict__ n_dev,
               int64_t n_max, bool packed, uint32_t *__restrict__ part, uint32_t *__restrict__ gathered) {
@@ -90,11 +118,11 @@ k_scan_reduce(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ 
         for (int k = 0; k < kScanItems; ++k) {
             const int64_t p = base + k * kScanBlock + threadIdx.x;
             if (p < b1) gathered[p] = c[k];  // read back contiguously by k_scan_apply
-            acc += c[k];
+            acc = add_sat(acc, c[k]);
         }
     }
     uint32_t tot;
-    block_exclusive_scan(acc, lds, tot);
+    block_exclusive_scan_sat(acc, lds, tot);
     if (threadIdx.x == 0) part[blockIdx.x] = tot;
 }
 
@@ -112,12 +140,12 @@ __device__ inline uint32_t partial_prefix(const uint32_t *__restrict__ part, int
     uint32_t before = 0u, every = 0u;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
-        every += v[q];
-        before += (int)threadIdx.x + q * kScanBlock < (int)blockIdx.x ? v[q] : 0u;
+        every = add_sat(every, v[q]);
+        before = add_sat(before, (int)threadIdx.x + q * kScanBlock < (int)blockIdx.x ? v[q] : 0u);
     }
     uint32_t pre;
-    block_exclusive_scan(before, lds, pre);
-    block_exclusive_scan(every, lds, all);
+    block_exclusive_scan_sat(before, lds, pre);
+    block_exclusive_scan_sat(every, lds, all);
     return pre;
 }
 
@@ -153,12 +181,12 @@ k_scan_apply(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ n
         for (int k = 0; k < kScanItems; ++k) sum += v[k];
         if (p0 < b1) large[p0 / 8] = large_bits(v);
         uint32_t tot;
-        uint32_t pre = running + block_exclusive_scan(sum, lds, tot);
+        uint32_t pre = add_sat(running, block_exclusive_scan_sat(sum, lds, tot));
         uint32_t o[kScanItems];
 #pragma unroll
         for (int k = 0; k < kScanItems; ++k) {
             o[k] = pre;
-            pre += v[k];
+            pre = add_sat(pre, v[k]);
         }
         if (whole) {
             *reinterpret_cast<uint4 *>(out + p0) = make_uint4(o[0], o[1], o[2], o[3]);
@@ -168,7 +196,7 @@ k_scan_apply(const uint32_t *__restrict__ counts, const uint32_t *__restrict__ n
             for (int k = 0; k < kScanItems; ++k)
                 if (p0 + k < b1) out[p0 + k] = o[k];
         }
-        running += tot;
+        running = add_sat(running, tot);
     }
 }
 
@@ -563,7 +591,7 @@ k_scan_offsets(const uint32_t *__restrict__ counts, const uint32_t *__restrict__
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) sum += v[k];
     uint32_t tot;
-    uint32_t pre = block_exclusive_scan(sum, lds, tot);
+    uint32_t pre = block_exclusive_scan_sat(sum, lds, tot);
     if (threadIdx.x < kWave) {
         const int lane = lane_id();
         if (lane == 0) store_status(status + blockIdx.x, (blockIdx.x == 0 ? kScanInc : kScanAgg) | (uint64_t)tot);
@@ -592,16 +620,16 @@ k_scan_offsets(const uint32_t *__restrict__ counts, const uint32_t *__restrict__
         if (lane == 0) {
             if (blockIdx.x > 0) store_status(status + blockIdx.x, kScanInc | (prefix + tot));
             earlier = prefix;
-            if (last) *total = (uint32_t)prefix + tot;
+            if (last) *total = (uint32_t)min(prefix + tot, 0xffffffffull);
         }
     }
     __syncthreads();
-    pre += (uint32_t)earlier;
+    pre = add_sat(pre, (uint32_t)min(earlier, 0xffffffffull));
     uint32_t o[kScanItems];
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         o[k] = pre;
-        pre += v[k];
+        pre = add_sat(pre, v[k]);
     }
     if (p0 < n) large[p0 / 8] = large_bits(v);
     if (whole) {
@@ -861,6 +889,8 @@ __device__ void emit_large(LargeList &ls, const uint32_t *__restrict__ sorted_re
         __syncthreads();
         for (uint32_t q = threadIdx.x / kWave; q < n_list; q += kKeygenWaves) {
             const uint32_t p = (uint32_t)__builtin_amdgcn_readfirstlane((int)ls.pos[q]);
+            uint32_t k0 = offsets[p];
+            if (k0 >= cap) continue;  // wave-uniform; no sum below passes 2^32
             const uint32_t r = sorted_rec[p] & rec_mask;
             const int v = (int)(r / (uint32_t)n_per_view);
             Footprint f;
@@ -869,7 +899,6 @@ __device__ void emit_large(LargeList &ls, const uint32_t *__restrict__ sorted_re
                 continue;  // wave-uniform
             const int T = vt.tile, sh = __builtin_ctz((unsigned)vt.tile);
             const uint32_t base = (uint32_t)vt.tile_off[v], tiles_x = (uint32_t)vt.tiles_x[v];
-            uint32_t k0 = offsets[p];
             for (int ty0 = f.j0 >> sh; ty0 <= f.j1 >> sh; ty0 += kWave) {
                 const int ty = ty0 + lane;
                 int ta = 0, tb = -1;
@@ -950,7 +979,7 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
         k = offsets[p];
     }
     const bool big = c > kBigRecord;
-    const bool own = act && c != 0u && !big;
+    const bool own = act && c != 0u && !big && k < cap;  // others emit nothing
     int v = 0, ty0 = 0, nr = 0;
     uint32_t base = 0, tiles_x = 0;
     uint4 sp = make_uint4(0u, 0u, 0u, 0u);
@@ -1003,7 +1032,7 @@ k_keygen(const uint32_t *__restrict__ sorted_rec, uint32_t rec_mask, const uint3
     // The run ends at the largest end of the wave's records (large ones included); lane 0
     // holds the wave's first record (if it has none, neither has any other lane).
     const uint32_t run0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
-    uint32_t end = act ? k + c : run0;
+    uint32_t end = act ? add_sat(k, c) : run0;
     for (int off = 32; off > 0; off >>= 1) end = max(end, (uint32_t)__shfl_xor((int)end, off, 64));
     if (end > cap) end = cap;
     const uint64_t le = (lane == kWave - 1) ? ~0ull : ((2ull << lane) - 1ull);  // lanes <= this one

@@ -98,7 +98,7 @@ __device__ inline void span_row(const uint4 sp, int rows, int i, int &ta, int &t
 
 // Frame-state layout (caller-owned device buffer).
 struct FrameHeader {
-    uint32_t pairs;     // tile pairs produced (or needed, on overflow)
+    uint32_t pairs;     // tile pairs produced (or needed, on overflow; at most 2^32 - 1)
     uint32_t overflow;  // nonzero if pairs > capacity
     uint32_t capacity;
     uint32_t tile;
@@ -428,7 +428,7 @@ constexpr uint32_t kPackCountMax = (1u << (32 - kPackShift)) - 1u;
 
 // Exclusive scan for p < min(*n_dev, n) of counts[idx[p]] or, with packed, of the pair count
 // packed in idx[p] (see kPackShift), which also go to gathered[p].  Writes offsets[p], the total
-// to *total, and to large a bit per p for counts above kBigRecord.  part: kScanMaxBlocks words of
+// to *total (both stop at 2^32 - 1), and to large a bit per p for counts above kBigRecord.  part: kScanMaxBlocks words of
 // scratch and then scan_status_words(n) that the caller clears (launch_preprocess does).
 // *stall as for radix_sort.
 int64_t scan_status_words(int64_t n);

@@ -119,7 +119,9 @@ class Rasterizer:
                 self.pairs = B.frame_status(fs, B.stream_handle())
                 return out, fs
             except B.CapacityError as e:
-                self.max_pairs = int(e.pairs * 1.25) + 1024
+                if e.pairs > B.MAX_PAIRS:
+                    raise  # no frame state holds as many
+                self.max_pairs = min(int(e.pairs * 1.25) + 1024, B.MAX_PAIRS)
 
     def check(self, frame_state=None):
         """Synchronise and read the status of a forward (by default the last one made through
@@ -132,7 +134,7 @@ class Rasterizer:
         try:
             self.pairs = B.frame_status(fs, B.stream_handle())
         except B.CapacityError as e:
-            self.max_pairs = int(e.pairs * 1.25) + 1024
+            self.max_pairs = min(int(e.pairs * 1.25) + 1024, B.MAX_PAIRS)
             raise
         return self.pairs
 
