@@ -6,11 +6,14 @@ width trade binning and sorting cost against per-pixel work, and the best choice
 on the window (view sizes, Gaussian count, footprint sizes).  ``autotune`` times whole
 mapping iterations (render, patch scale + loss, backward) of every candidate on the
 caller's own data and returns the fastest configuration.  Choices are cached in a JSON
-file keyed by device, window geometry, Gaussian count and pointmap frame.
+file keyed by device, window geometry, Gaussian count, the settings that select kernels and
+the library's contents: another build's kernels may prefer another shape.
 """
 from __future__ import annotations
 
 import dataclasses
+import functools
+import hashlib
 import json
 import os
 from typing import Iterable, List, Optional, Sequence, Tuple
@@ -30,10 +33,22 @@ def default_candidates(digit_bits: Sequence[int] = (6, 7, 8)) -> List[Candidate]
     return [(t, p, d) for (t, p) in B.RasterConfig.SHAPES for d in digit_bits]
 
 
+@functools.lru_cache(maxsize=4)
+def _file_hash(path: str, mtime_ns: int, size: int) -> str:
+    with open(path, "rb") as fh:
+        return hashlib.sha256(fh.read()).hexdigest()[:16]
+
+
+def _library() -> str:
+    st = os.stat(B.LIB_PATH)
+    return _file_hash(B.LIB_PATH, st.st_mtime_ns, st.st_size)
+
+
 def cache_key(win: Window, n_gaussians: int, cfg: B.RasterConfig) -> str:
     dev = torch.cuda.get_device_name(win.T_cw.device)
     views = ";".join(f"{w}x{h}" for (h, w) in win.sizes)
-    return f"{dev}|{views}|n={n_gaussians}|frame={cfg.pointmap_frame}"
+    kernels = f"{int(cfg.bwd_lane_reduce != 0)}{int(cfg.count_work != 0)}{int(cfg.mark_visible != 0)}"
+    return f"{dev}|{views}|n={n_gaussians}|frame={cfg.pointmap_frame}|kernels={kernels}|lib={_library()}"
 
 
 def _load_cache(path: Optional[str]) -> dict:
