@@ -82,7 +82,7 @@ __device__ inline double fold_patch(double x, double *lds, int lane, int P, int 
 // waves per SIMD hold that many; taller patches read the rest again).  Reading the pointmaps
 // once and taking each root once leaves loads and float64 divisions about equal: 8 views with
 // 3.7M pixels, patch 10: 57 us with the rows read three times, 36 us now.
-constexpr int kKeepRows = 12;
+constexpr int kKeepRows = 12, kReadRows = 4;
 
 __global__ void __launch_bounds__(kAlignBlock) __attribute__((amdgpu_waves_per_eu(4)))
 k_align_stats(ViewTable vt, AlignStrips st, const float *__restrict__ Xr, const float *__restrict__ Xp,
@@ -120,15 +120,28 @@ k_align_stats(ViewTable vt, AlignStrips st, const float *__restrict__ Xr, const 
             used |= 1u << k;
         }
     }
-    // Calls f(|X^r|, |X^p|) for every selected pixel of the column, top to bottom.
+    // Calls f(|X^r|, |X^p|) for every selected pixel of the column, top to bottom.  The rows
+    // that are not kept are read kReadRows at a time, without a branch around a load (rows past
+    // the patch read its last one), so that their latencies overlap.
     auto each = [&](auto f) {
 #pragma unroll
         for (int k = 0; k < kKeepRows; ++k)
             if ((used >> k) & 1u) f(nr[k], np[k]);
-        for (int k = kKeepRows; k < rows; ++k) {
-            const int64_t e = (int64_t)k * W;
-            if (m0 && m0[e] == 0.f) continue;
-            f(norm3(r0, e, plane), norm3(p0, e, plane));
+        for (int k = kKeepRows; k < rows; k += kReadRows) {
+            float xr[kReadRows][3], xp[kReadRows][3], m[kReadRows];
+#pragma unroll
+            for (int q = 0; q < kReadRows; ++q) {
+                const int64_t e = (int64_t)min(k + q, rows - 1) * W;
+                m[q] = m0 ? m0[e] : 1.0f;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    xr[q][c] = r0[e + c * plane];
+                    xp[q][c] = p0[e + c * plane];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < kReadRows; ++q)
+                if (k + q < rows && m[q] != 0.f) f(norm3(xr[q], 0, 1), norm3(xp[q], 0, 1));
         }
     };
 
