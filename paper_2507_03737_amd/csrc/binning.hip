@@ -1119,7 +1119,10 @@ hipError_t launch_compact(uint32_t *counts, const uint32_t *dkey, const uint64_t
     const float4 *rec = reinterpret_cast<const float4 *>(records);
     const Segments sg = {live, live + n_segs, (uint32_t)n_segs, (uint32_t)nw, n_per_view};
     const unsigned nb = (unsigned)std::min<int64_t>((n_segs + kSegTile - 1) / kSegTile, kScanMaxBlocks);
-    const unsigned nbig = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(64, n_segs / 8));
+    // Blocks that count the large records: a segment each until the chip is full, as all of a small
+    // window's may be large (32 views of 320x240 with 1000 Gaussians at 8 x 8 tiles: 36 us with a
+    // block for 8 segments, 11 so; none where few are large).
+    const unsigned nbig = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(64, n_segs));
     const bool direct = n_segs <= kDirectSegs;
     if (!direct)
         hipLaunchKernelGGL(k_live_reduce, dim3(nb + nbig), dim3(kScanBlock), 0, s, sg, rec, vt, rs, counts, nb, part);
@@ -1233,7 +1236,9 @@ hipError_t launch_keygen(const uint32_t *sorted_rec, uint32_t rec_mask, const ui
     // Enough blocks for the records, and for the clearing where there are few of them.
     const int64_t clears = clr.n_tiles + clr.n_visible + clr.n_wmask;
     const int64_t nb = std::max<int64_t>(std::max<int64_t>(1, (n_records + 255) / 256), std::min<int64_t>(512, clears / 2048));
-    const int64_t nbig = n_records > 0 ? std::min<int64_t>(1024, std::max<int64_t>(64, n_records / 512)) : 0;
+    // Likewise for the large records' pairs: 32 records to a block (the window above: 165 us with 512,
+    // 43 so).
+    const int64_t nbig = n_records > 0 ? std::min<int64_t>(1024, std::max<int64_t>(64, n_records / 32)) : 0;
     // One launch for both where launches count (500k records: 45 us against 55), two where the
     // large records' blocks only lengthen the end (8M: 188 us against 191, 48M: 1.46 against 1.48 ms).
     const bool together = n_records <= kScanSmall;

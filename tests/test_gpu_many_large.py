@@ -1,0 +1,45 @@
+"""Small windows in which every record is large: counted and emitted by enough workgroups.
+
+Each of 32 small views sees 1000 Gaussians of more than 64 tiles at 8 x 8.  The window's pairs are the
+sum of the views' alone, and emitting them takes no longer than sorting them (the emission writes
+each pair once, the sort reads and writes it three times; with 64 workgroups for all large records
+the emission took longer).
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+from paper_2507_03737_amd import binding  # noqa: E402
+from paper_2507_03737_amd.render import Rasterizer, Window  # noqa: E402
+from paper_2507_03737_amd.scenes import Camera  # noqa: E402
+
+from . import gpu_util as U  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def run(views, scale, n=1000):
+    rng = np.random.default_rng(7)
+    f32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()  # noqa: E731
+    z = rng.uniform(2.0, 6.0, n)
+    params = (f32(np.stack([rng.uniform(-.5, .5, n) * z, rng.uniform(-.4, .4, n) * z, z])), f32(np.full((3, n), scale)),
+              f32(rng.normal(size=(4, n))), f32(rng.normal(-1, 1, n)), f32(rng.uniform(0, 1, (3, n))))
+    T = f32(np.tile([1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0], (views, 1)))
+    rast = Rasterizer(Window([Camera(320, 240, 256.0, 256.0, 160.0, 120.0)] * views, T), n, binding.RasterConfig(tile=8))
+    rast.forward(params)
+    rast.max_pairs = int(rast.pairs * 1.3) + 4096
+    out, fs = rast.forward(params)
+    for timing in (False, True):
+        rast.ctx.timing(timing)
+        for _ in range(10):
+            rast.forward_into(params, out, fs)
+    t = rast.ctx.collect_timing()
+    return rast.pairs, *(t[k][0] / t[k][1] for k in ("binning", "tile_sort"))
+
+
+def test_many_large_records():
+    U.log("[gpu] many large records")
+    pairs, emit, sort = run(32, -1.0)
+    U.log(f"  {pairs} pairs emitted in {emit * 1e3:.1f} us, sorted in {sort * 1e3:.1f} us")
+    assert pairs == 32 * run(1, -1.0)[0] and pairs > 64 * 32000
+    assert emit <= sort
