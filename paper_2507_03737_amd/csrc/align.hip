@@ -290,14 +290,18 @@ k_align_iterate(AlignStrips st, const AlignPatch *__restrict__ patches, double d
 
 // Eq. 14: keep X^r where |X^r - s X^p| <= eps_m |s X^p|, else take s X^p.  Bound by memory
 // traffic (36 bytes per pixel), four pixels per lane and step where the planes allow 16-byte
-// accesses (aligned16, and W H a multiple of 4).  Atomics on one cache line take 9 ns each
+// accesses (wide, and W H a multiple of 4).  Atomics on one cache line take 9 ns each
 // whatever their number, so the grid is two workgroups per compute unit: 8 views with 3.7M
-// pixels: 170 us with one update per 256 pixels, 23 us now (5.7 TB/s, some of it cached).
-constexpr int kReplaceBlock = 512, kReplaceBlocks = 512;
+// pixels: 170 us with one update per 256 pixels, 23 us now (5.7 TB/s, some of it cached).  Large
+// windows take more workgroups, a view's side by side (fewer streams at a time through the
+// memory: 16 views of 1920x1080 251 us with 512, 227 with 4096), and beyond 12M pixels one pixel
+// per lane, for the same reason (218 us).
+constexpr int kReplaceBlock = 512, kReplaceBlocks = 512, kReplaceMost = 4096;
+constexpr int64_t kReplacePixels = 8192, kReplaceWide = 12 << 20;
 
 __global__ void __launch_bounds__(kReplaceBlock)
 k_replace(ViewTable vt, const float *__restrict__ Xr, const float *__restrict__ Xp,
-          const gspm_align_result *__restrict__ res, double eps_m, bool aligned16, float *__restrict__ out,
+          const gspm_align_result *__restrict__ res, double eps_m, bool wide, float *__restrict__ out,
           uint32_t *__restrict__ replaced) {
     const int v = blockIdx.y;
     const int64_t plane = (int64_t)vt.width[v] * vt.height[v], o3 = 3 * vt.pix_off[v];
@@ -315,7 +319,7 @@ k_replace(ViewTable vt, const float *__restrict__ Xr, const float *__restrict__ 
         cnt += rep ? 1u : 0u;
     };
     const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
-    if (aligned16 && plane % 4 == 0 && o3 % 4 == 0) {
+    if (wide && plane % 4 == 0 && o3 % 4 == 0) {
         for (int64_t e = 4 * first; e < plane; e += 4 * step) {
             float4 r[3], p[3], o[3];
 #pragma unroll
@@ -384,11 +388,13 @@ hipError_t launch_replace(const ViewTable &vt, const float *Xr, const float *Xp,
     if (e != hipSuccess) return e;
     int64_t maxp = 1;
     for (int v = 0; v < vt.n_views; ++v) maxp = std::max<int64_t>(maxp, (int64_t)vt.width[v] * vt.height[v]);
+    const int64_t pixels = vt.pix_off[vt.n_views];
+    const bool wide = (((uintptr_t)Xr | (uintptr_t)Xp | (uintptr_t)out) & 15u) == 0u && pixels <= kReplaceWide;
+    const int64_t most = std::min<int64_t>(kReplaceMost, std::max<int64_t>(kReplaceBlocks, pixels / kReplacePixels));
     const int64_t bx = std::min<int64_t>((maxp + 4 * kReplaceBlock - 1) / (4 * kReplaceBlock),
-                                         std::max(1, kReplaceBlocks / vt.n_views));
-    const bool aligned16 = (((uintptr_t)Xr | (uintptr_t)Xp | (uintptr_t)out) & 15u) == 0u;
+                                         std::max<int64_t>(1, most / vt.n_views));
     hipLaunchKernelGGL(k_replace, dim3((unsigned)bx, (unsigned)vt.n_views), dim3(kReplaceBlock), 0, s, vt, Xr, Xp,
-                       result, (double)eps_m, aligned16, out, replaced);
+                       result, (double)eps_m, wide, out, replaced);
     return hipGetLastError();
 }
 
