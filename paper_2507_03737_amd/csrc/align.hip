@@ -61,7 +61,7 @@ __device__ inline double norm3(const float *X, int64_t a, int64_t plane) {
 
 // Makes a wave's LDS writes visible to its other lanes.
 __device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
 

@@ -177,7 +177,7 @@ k_pnp_hyp(const float *__restrict__ X, const float *__restrict__ uv, int64_t n, 
         A[l] = acc;
         E[l] = i == j ? 1.0 : 0.0;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     // Cyclic Jacobi in rounds of six disjoint rotations (a round-robin schedule: 11 rounds meet
     // every pair once): a serial chain of 11 angles a sweep instead of the 66 of single
@@ -277,7 +277,7 @@ k_pnp_hyp(const float *__restrict__ X, const float *__restrict__ uv, int64_t n, 
                 A[pj * 12 + qi] = n10;
                 A[qj * 12 + qi] = n11;
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
     }
