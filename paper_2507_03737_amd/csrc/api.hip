@@ -69,7 +69,7 @@ struct gspm_ctx {
     size_t used = 0;
     std::vector<int> phase_of;  // per recorded pair
     // Per record (n * V).
-    DevBuf counts, big, live, dkey, dval, dkey_tmp, dval_tmp, dkey_s, dval_s, offsets, grad2d, spans;
+    DevBuf counts, words, cval, dkey, dval, dkey_tmp, dval_tmp, dkey_s, dval_s, offsets, grad2d, spans;
     // The image-plane gradient rows are all zero: the parameter pass clears every row it
     // reads as nonzero, so only a new allocation or an interrupted backward needs a fill.
     bool grad2d_clean = false;
@@ -208,8 +208,8 @@ hipError_t ensure_records(gspm_ctx *c, int64_t R, int digit_bits) {
     hipError_t e;
     if ((e = grow(c->counts, 4 * w))) return e;
     // Live and large bits of every 64 records of a view, then the large bits in depth order.
-    if ((e = grow(c->big, 8 * (3 * (w / kWave) + 2 * kMaxViews + 1)))) return e;
-    if ((e = grow(c->live, 4 * w))) return e;
+    if ((e = grow(c->words, 8 * (3 * (w / kWave) + 2 * kMaxViews + 1)))) return e;
+    if ((e = grow(c->cval, 4 * w))) return e;
     if ((e = grow(c->dkey, 4 * w))) return e;
     if ((e = grow(c->dval, 4 * w))) return e;
     if ((e = grow(c->dkey_tmp, 4 * w))) return e;
@@ -310,7 +310,7 @@ gspm_status gspm_create(gspm_ctx **out) {
 
 void gspm_destroy(gspm_ctx *ctx) {
     if (!ctx) return;
-    DevBuf *bufs[] = {&ctx->counts, &ctx->big, &ctx->live, &ctx->dkey, &ctx->dval, &ctx->dkey_tmp, &ctx->dval_tmp,
+    DevBuf *bufs[] = {&ctx->counts, &ctx->words, &ctx->cval, &ctx->dkey, &ctx->dval, &ctx->dkey_tmp, &ctx->dval_tmp,
                       &ctx->dkey_s, &ctx->dval_s, &ctx->offsets, &ctx->grad2d, &ctx->spans, &ctx->pkey, &ctx->pval,
                       &ctx->pkey_tmp, &ctx->pval_tmp, &ctx->pkey_s, &ctx->hist, &ctx->scan_part, &ctx->misc,
                       &ctx->pose_part, &ctx->loss_part, &ctx->align, &ctx->aux, &ctx->pnp, &ctx->twork};
@@ -397,7 +397,7 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
     // 1. Project every (Gaussian, view) record.
     PhaseTimer t_pre(ctx, hs, GSPM_PHASE_PREPROCESS);
     const int64_t n_per_view = g->n > 0 ? g->n : 1;
-    uint64_t *live = static_cast<uint64_t *>(ctx->big.p);
+    uint64_t *live = static_cast<uint64_t *>(ctx->words.p);
     uint8_t *large = reinterpret_cast<uint8_t *>(live + 2 * P.vt.n_views * live_waves(n_per_view));  // in depth order
     GSPM_HIP(launch_preprocess(*g, P.vt, views->T_cw, P.rs, records, counts, static_cast<uint32_t *>(ctx->dkey.p),
                                static_cast<uint4 *>(ctx->spans.p), live, &hdr->sort_stall, hist, radix_total_words(db),
@@ -413,12 +413,12 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
         //    depth (stable, so ties keep record order).
         PhaseTimer t_ds(ctx, hs, GSPM_PHASE_DEPTH_SORT);
         GSPM_HIP(launch_compact(counts, static_cast<uint32_t *>(ctx->dkey.p), live, records, P.vt, P.rs, n_per_view,
-                                static_cast<uint32_t *>(ctx->dval.p), static_cast<uint32_t *>(ctx->live.p), n_live,
+                                static_cast<uint32_t *>(ctx->dval.p), static_cast<uint32_t *>(ctx->cval.p), n_live,
                                 part, pack, hs));
-        GSPM_HIP(radix_sort(static_cast<uint32_t *>(ctx->dval.p), static_cast<uint32_t *>(ctx->live.p),
+        GSPM_HIP(radix_sort(static_cast<uint32_t *>(ctx->dval.p), static_cast<uint32_t *>(ctx->cval.p),
                             static_cast<uint32_t *>(ctx->dkey_tmp.p), static_cast<uint32_t *>(ctx->dval_tmp.p),
                             static_cast<uint32_t *>(ctx->dkey_s.p), static_cast<uint32_t *>(ctx->dval_s.p), R, n_live,
-                            32, db, hist, &hdr->sort_stall, nullptr, hs, false));
+                            32, db, hist, &hdr->sort_stall, nullptr, hs));
         t_ds.stop();
     }
     PhaseTimer t_bin(ctx, hs, GSPM_PHASE_BINNING);
@@ -458,7 +458,7 @@ gspm_status gspm_render_forward(gspm_ctx *ctx, const gspm_gaussians *g, const gs
         GSPM_HIP(radix_sort(static_cast<uint32_t *>(ctx->pkey.p), static_cast<uint32_t *>(ctx->pval.p),
                             static_cast<uint32_t *>(ctx->pkey_tmp.p), static_cast<uint32_t *>(ctx->pval_tmp.p),
                             static_cast<uint32_t *>(ctx->pkey_s.p), pair_vals, cap, &hdr->pairs,
-                            tile_bits(P.n_tiles), db, hist, &hdr->sort_stall, ranges, hs, false));
+                            tile_bits(P.n_tiles), db, hist, &hdr->sort_stall, ranges, hs));
         t_ts.stop();
     }
     // Heaviest tiles first: by list length for the forward; the forward measures each

@@ -824,7 +824,7 @@ k_radix_pass(const uint32_t *__restrict__ kin, const uint32_t *__restrict__ vin,
         const uint32_t k = key[st];
         const uint32_t d = (k >> shift) & (R - 1);
         const uint32_t pos = gbase[d] + ((uint32_t)j - dstart[d]);
-        if (kout) kout[pos] = k;  // the last pass may drop the keys: only the values are used
+        if (kout) kout[pos] = k;  // the last pass drops the keys: only the values are used
         vout[pos] = lk[j];
     }
 }
@@ -1157,7 +1157,7 @@ int radix_total_words(int digit_bits) { return kSortMaxPasses << digit_bits; }
 template <int DB, int STEPS>
 static void sort_passes(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_tmp, uint32_t *vals_tmp,
                         uint32_t *keys_out, uint32_t *vals_out, int64_t n_max, const uint32_t *n_dev, int passes,
-                        uint32_t *scratch, uint32_t *stall, uint2 *ranges, bool keep_keys, hipStream_t s) {
+                        uint32_t *scratch, uint32_t *stall, uint2 *ranges, hipStream_t s) {
     constexpr int R = 1 << DB;
     const int64_t tiles = sort_tiles(n_max);
     uint32_t *ghist = scratch;
@@ -1183,7 +1183,7 @@ static void sort_passes(const uint32_t *keys_in, const uint32_t *vals_in, uint32
         uint32_t *ko = to_out ? keys_out : keys_tmp;
         uint32_t *vo = to_out ? vals_out : vals_tmp;
         hipLaunchKernelGGL((k_radix_pass<DB, STEPS>), dim3((unsigned)tiles), dim3(kSortBlock), 0, s, kin, vin,
-                           p == passes - 1 && !keep_keys ? nullptr : ko, vo, n_dev,
+                           p == passes - 1 ? nullptr : ko, vo, n_dev,
                            n_max, p * DB, ghist + (int64_t)p * R, status[p & 1], status[(p + 1) & 1], stall,
                            p == passes - 1 ? ranges : nullptr, p == 0 ? tprefix : nullptr, tiles);
         kin = ko;
@@ -1193,8 +1193,7 @@ static void sort_passes(const uint32_t *keys_in, const uint32_t *vals_in, uint32
 
 hipError_t radix_sort(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_tmp, uint32_t *vals_tmp,
                       uint32_t *keys_out, uint32_t *vals_out, int64_t n_max, const uint32_t *n_dev, int bits,
-                      int digit_bits, uint32_t *scratch, uint32_t *stall, uint2 *ranges, hipStream_t s,
-                      bool keep_keys) {
+                      int digit_bits, uint32_t *scratch, uint32_t *stall, uint2 *ranges, hipStream_t s) {
     if (n_max <= 0) return hipSuccess;
     if (bits < 1) bits = 1;
     if (digit_bits < 4 || digit_bits > 8) return hipErrorInvalidValue;
@@ -1206,7 +1205,7 @@ hipError_t radix_sort(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t
     if (db < 4) db = 4;
 #define GSPM_SORT(DB, STEPS)                                                                                     \
     sort_passes<DB, STEPS>(keys_in, vals_in, keys_tmp, vals_tmp, keys_out, vals_out, n_max, n_dev, passes, scratch, \
-                           stall, ranges, keep_keys, s)
+                           stall, ranges, s)
 #define GSPM_SORT_DB(DB)                          \
     do {                                          \
         if (steps == 4) GSPM_SORT(DB, 4);         \

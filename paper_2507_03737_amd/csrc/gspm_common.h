@@ -164,25 +164,6 @@ __device__ inline int lane_id() { return __lane_id(); }
 // an int and back, which costs two vector instructions per call.
 __device__ inline uint64_t ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 
-// Sum over the 64 lanes of a wave using DPP row operations; the total lands in lane 63.
-#define GSPM_DPP(x, ctrl, rmask)                                                            \
-    __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (x)), \
-                                                          (ctrl), (rmask), 0xf, false))
-
-__device__ inline float wave_sum_to_lane63(float x) {
-    x += GSPM_DPP(x, 0xb1, 0xf);   // quad_perm [1,0,3,2]
-    x += GSPM_DPP(x, 0x4e, 0xf);   // quad_perm [2,3,0,1]
-    x += GSPM_DPP(x, 0x114, 0xf);  // row_shr:4
-    x += GSPM_DPP(x, 0x118, 0xf);  // row_shr:8
-    x += GSPM_DPP(x, 0x142, 0xa);  // row_bcast:15 into rows 1 and 3
-    x += GSPM_DPP(x, 0x143, 0xc);  // row_bcast:31 into rows 2 and 3
-    return x;
-}
-
-__device__ inline float wave_total(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_to_lane63(x)), 63));
-}
-
 #define GSPM_DPP_MOV(x, ctrl)                                                              \
     __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, (x)), \
                                                           (ctrl), 0xf, 0xf, true))
@@ -302,20 +283,6 @@ __device__ inline uint32_t wave_inclusive_scan(uint32_t x) {
         if (lane >= d) x += y;
     }
     return x;
-}
-
-// Appends the lanes with pred set to a global queue with one atomic per wave; returns
-// each such lane's slot.  Must be reached by every active lane of the wave.
-__device__ inline uint32_t wave_append(uint32_t *counter, bool pred) {
-    const uint64_t m = ballot(pred);
-    if (m == 0ull) return 0u;
-    const int lane = lane_id();
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    uint32_t base = 0u;
-    if (lane == leader) base = atomicAdd(counter, (uint32_t)__popcll(m));
-    base = (uint32_t)__shfl((int)base, leader, kWave);
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    return base + (uint32_t)__popcll(m & lt);
 }
 
 __device__ inline int find_view(const ViewTable &vt, int32_t global_tile) {
@@ -446,19 +413,18 @@ hipError_t launch_compact(uint32_t *counts, const uint32_t *dkey, const uint64_t
 // Stable LSD radix sort of (key, value) uint32 pairs over the low `bits` key bits, in
 // ceil(bits / digit_bits) passes of equal width (digit_bits in [4, 8]).  n_dev: device
 // count (may be NULL: n_max is then exact).  Buffers: keys/vals in, tmp, out (the sorted
-// result ends in keys_out/vals_out).  scratch: radix_hist_words(n_max, digit_bits) words, of which
+// values end in vals_out; keys_out holds an earlier pass's keys).  scratch: radix_hist_words(n_max, digit_bits) words, of which
 // the caller clears the first radix_total_words(digit_bits) (launch_preprocess and launch_keygen do).
 // *stall (device) is set if a pass gave up waiting for an earlier tile (the result is
 // then invalid); the caller clears it.  ranges (optional): the keys are tile ids and the
 // final pass writes each tile's [first, end) positions; the caller fills it with
-// (0xffffffff, 0) beforehand, which empty tiles keep.  keep_keys = false: the final pass
-// writes only the values (keys_out then holds an earlier pass's keys).
+// (0xffffffff, 0) beforehand, which empty tiles keep.
 int64_t radix_hist_words(int64_t n_max, int digit_bits);
 int radix_total_words(int digit_bits);
 hipError_t radix_sort(const uint32_t *keys_in, const uint32_t *vals_in, uint32_t *keys_tmp,
                       uint32_t *vals_tmp, uint32_t *keys_out, uint32_t *vals_out, int64_t n_max,
                       const uint32_t *n_dev, int bits, int digit_bits, uint32_t *scratch, uint32_t *stall,
-                      uint2 *ranges, hipStream_t s, bool keep_keys = true);
+                      uint2 *ranges, hipStream_t s);
 
 // What the emission clears for later kernels, to save their launches: the tile ranges (given to it
 // as such), the per-tile work, the tile sort's digit totals, the visible marks and the
