@@ -295,7 +295,7 @@ k_align_iterate(AlignStrips st, const AlignPatch *__restrict__ patches, double d
 // pixels: 170 us with one update per 256 pixels, 23 us now (5.7 TB/s, some of it cached).  Large
 // windows take more workgroups, a view's side by side (fewer streams at a time through the
 // memory: 16 views of 1920x1080 251 us with 512, 227 with 4096), and beyond 12M pixels one pixel
-// per lane, for the same reason (218 us).
+// per lane, for the same reason (221 us).
 constexpr int kReplaceBlock = 512, kReplaceBlocks = 512, kReplaceMost = 4096;
 constexpr int64_t kReplacePixels = 8192, kReplaceWide = 12 << 20;
 

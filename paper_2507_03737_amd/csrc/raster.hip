@@ -942,8 +942,8 @@ constexpr int kOutPitch = 20;            // floats of an entry's sums: 16-byte w
 // 1.17 ms and 207 us, but their gradients lay 2 to 4 times further from these than two runs of one
 // form from each other.)
 //
-// Vector issue and the matrix cores (32 cycles per entry) share its time.  8 views with 1M
-// Gaussians: 1.40 ms before (workgroups, entries one by one, 16x16x4 products: 64 cycles per
+// Vector issue (38 instructions per entry and wave), the matrix cores (32 cycles) and the LDS (26
+// cycles, 56% of its time) bind it together.  8 views with 1M Gaussians: 1.40 ms before (workgroups, entries one by one, 16x16x4 products: 64 cycles per
 // entry), 1.17 ms now; pose-only at 960x640 with 500k: 274 and 207 us.  Four waves per SIMD fit
 // the LDS.
 template <int TILE, bool POSE_ONLY, int FRAME>
@@ -1249,11 +1249,14 @@ bool raster_config_supported(int tile, int ppt) {
 
 // Windows of at most this many waves (at one pixel per lane) are composited by independent
 // waves, larger ones by workgroups that share their staging.  The chip holds 5120 of these
-// waves at once; up to about ten rounds of them the longest waves' latency decides (960x640
-// with 500k Gaussians, 9.6k waves: 135 against 191 us; 1216x352 with 300k, 6.7k waves: 68
-// against 103 us), at 58k waves (8 keyframes, 1M Gaussians) the two take the same time (656 and
-// 667 us: vector issue binds both), and at 522k (16 x 1920x1080, 3M Gaussians) the second
-// reading of each record by every wave costs 6% (4.47 against 4.21 ms).
+// waves at once; up to about ten rounds of them the longest waves' latency decides (16 x 16 tiles,
+// 960x640 with 500k Gaussians, 9.6k waves: 118 against 194 us; 1216x352 with 300k, 6.7k waves: 63
+// against 103 us), at 58k waves (8 keyframes, 1M Gaussians) the two take the same time (645 and
+// 655 us: vector issue binds both).  Beyond, the second reading of each record by every wave costs
+// more the more waves there are (views of 1920x1080, waves against workgroups): 65k 0.527 and
+// 0.523 ms, 98k 0.828 and 0.810, 131k 1.07 and 1.05, 261k 2.16 and 2.12, 522k 4.38 and 4.18.
+// (Other tiles cross later: 32 x 32 at 98k 0.87 and 0.97 ms, 196k 1.74 and 1.89; 8 x 8 at 97k
+// 0.83 and 0.86.)
 constexpr int64_t kIndependentWaves = 65536;
 
 hipError_t launch_raster_forward(const ViewTable &vt, const RasterSettings &rs, const uint2 *ranges,
