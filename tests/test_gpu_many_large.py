@@ -29,12 +29,14 @@ def run(views, scale, n=1000):
     rast.forward(params)
     rast.max_pairs = int(rast.pairs * 1.3) + 4096
     out, fs = rast.forward(params)
-    for timing in (False, True):
-        rast.ctx.timing(timing)
-        for _ in range(10):
+    best = {}
+    rast.ctx.timing(True)
+    for _ in range(8):  # the fastest of 8 runs of 3 launches
+        for _ in range(3):
             rast.forward_into(params, out, fs)
-    t = rast.ctx.collect_timing()
-    return rast.pairs, *(t[k][0] / t[k][1] for k in ("binning", "tile_sort"))
+        for k, (ms, launches) in rast.ctx.collect_timing().items():
+            best[k] = min(best.get(k, 1e9), ms / max(1, launches))
+    return rast.pairs, best["binning"], best["tile_sort"]
 
 
 def test_many_large_records():
