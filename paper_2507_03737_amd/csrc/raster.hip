@@ -943,9 +943,10 @@ constexpr int kOutPitch = 20;            // floats of an entry's sums: 16-byte w
 // form from each other.)
 //
 // Vector issue (38 instructions per entry and wave), the matrix cores (32 cycles) and the LDS (26
-// cycles, 56% of its time) bind it together.  8 views with 1M Gaussians: 1.40 ms before (workgroups, entries one by one, 16x16x4 products: 64 cycles per
-// entry), 1.17 ms now; pose-only at 960x640 with 500k: 274 and 207 us.  Four waves per SIMD fit
-// the LDS.
+// cycles, 57% of its time) bind it together.  8 views with 1M Gaussians: 1.40 ms before
+// (workgroups, entries one by one, 16x16x4 products: 64 cycles per entry), 1.17 ms now; pose-only
+// at 960x640 with 500k: 274 and 207 us.  Four waves per SIMD fit the LDS.  (Moments accumulated in
+// float64 rows, which would take the order of the atomics out of the gradients: 1.95 ms.)
 template <int TILE, bool POSE_ONLY, int FRAME>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(4)))
 k_raster_bwd_waves(ViewTable vt, RasterSettings rs, const uint2 *__restrict__ ranges,
